@@ -901,8 +901,9 @@ kv_status kv_rebuild_execute(const kv_weights* w, kv_plan_t plan, void* stream) 
       g.epi.q_out = Q;
       g.epi.arena_k = plane_k;
       g.epi.arena_v = plane_v;
-      g.epi.vt = VT;
-      g.epi.kc = KC;
+      // the last layer has no attention to copy its K/V for
+      g.epi.vt = last ? nullptr : VT;
+      g.epi.kc = last ? nullptr : KC;
       g.epi.ldvt = L.Wkpad;
       g.epi.krow = krow;
       g.epi.slot = slot;

@@ -839,20 +839,17 @@ bool launch_gemm_bf16_rows(const GemmParams& p, float* out, int64_t ldo, hipStre
 }
 
 void launch_gemm_bf16(int epi, const GemmParams& p_in, hipStream_t s) {
+  if (epi != EPI_STORE) {
+    launch_gemm_wide(epi, p_in, s);
+    return;
+  }
   const int tiles_m = (p_in.M + BM - 1) / BM;
   const int tiles_n = n_tiles_of(p_in);
   const dim3 grid(tiles_m * tiles_n), block(NT);
   if (p_in.M <= 0 || tiles_n <= 0) return;
   GemmParams p = p_in;
   p.group_m = group_m_for(tiles_n);
-  if (epi == EPI_QKV)
-    hipLaunchKernelGGL(gemm_bf16_kernel<EPI_QKV>, grid, block, 0, s, p, tiles_m, tiles_n);
-  else if (epi == EPI_RESID)
-    hipLaunchKernelGGL(gemm_bf16_kernel<EPI_RESID>, grid, block, 0, s, p, tiles_m, tiles_n);
-  else if (epi == EPI_STORE)
-    hipLaunchKernelGGL(gemm_bf16_kernel<EPI_STORE>, grid, block, 0, s, p, tiles_m, tiles_n);
-  else
-    hipLaunchKernelGGL(gemm_bf16_kernel<EPI_SWIGLU>, grid, block, 0, s, p, tiles_m, tiles_n);
+  hipLaunchKernelGGL(gemm_bf16_kernel<EPI_STORE>, grid, block, 0, s, p, tiles_m, tiles_n);
 }
 
 }  // namespace kvr

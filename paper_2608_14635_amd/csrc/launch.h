@@ -81,6 +81,7 @@ int launch_probe(int* dev_flag, hipStream_t s);
 
 // GEMMs with fused epilogues
 void launch_gemm_bf16(int epi, const GemmParams& p, hipStream_t s);
+void launch_gemm_wide(int epi, const GemmParams& p, hipStream_t s);  // EPI_QKV, EPI_RESID, EPI_SWIGLU
 void launch_gemm_f32(int epi, const GemmParams& p, hipStream_t s);
 // Few-row products (the decode step): K split over enough workgroups to fill
 // the chip, fp32 partials summed in split order by a second kernel that then
