@@ -1,7 +1,7 @@
 // C ABI of the KV-rebuild library: argument validation, wave planning,
 // metadata staging and the per-layer kernel sequence of the rebuild and of the
 // resumed decode step.  Host code only; the kernels live in misc.hip,
-// gemm_bf16.hip, gemm_f32.hip, attention.hip and decode.hip.
+// gemm_wide.hip, gemm_tile.hip, gemm_skinny.hip, gemm_f32.hip, attention.hip and decode.hip.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1192,10 +1192,12 @@ kv_status kv_decode_step(const kv_weights* w, const void* final_norm, const void
   };
   auto gemm_full = dt == KV_BF16 ? launch_gemm_bf16 : launch_gemm_f32;
   // a residual product and the RMSNorm of the updated rows with `gain`: one
-  // kernel after the bf16 few-row product, else the product and the norm
+  // kernel sums the bf16 partials and norms; fp32 models take them in turn
   auto resid_norm = [&](const GemmParams& gp, const void* gain) {
-    if (dt == KV_BF16 && launch_gemm_bf16_splitk_resid_norm(gp, gpart, L.gpart_elems, gain, A, eps, s))
+    if (dt == KV_BF16) {
+      launch_gemm_bf16_splitk_resid_norm(gp, gpart, L.gpart_elems, gain, A, eps, s);
       return;
+    }
     gemm(EPI_RESID, gp, s);
     launch_rmsnorm(dt, X, gain, A, R, H, eps, s);
   };

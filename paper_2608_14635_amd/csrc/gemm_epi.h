@@ -82,6 +82,7 @@ __device__ __forceinline__ void acc_resid(const f32x4 (&acc)[RI][CJ], int M, con
 template <int RI, int CJ, typename Row, typename Col>
 __device__ __forceinline__ void acc_swiglu(const f32x4 (&acc)[RI][CJ], int M, const EpiParams& e, Row row,
                                            Col col) {
+#pragma clang fp contract(off)
 #pragma unroll
   for (int i = 0; i < RI; ++i)
     if (row(i) < M) {
@@ -108,6 +109,9 @@ __device__ __forceinline__ void acc_swiglu(const f32x4 (&acc)[RI][CJ], int M, co
 template <int RI, int CJ, int BM, int BN, int WAVES, int WR, typename Row, typename Col>
 __device__ __forceinline__ void acc_qkv(f32x4 (&acc)[RI][CJ], int m0, int M, int n0, const EpiParams& e,
                                         char* smem, int wave, int lane, Row row, Col col) {
+  // every tile's instance has to round alike, so no product is contracted into
+  // an FMA but those written as one
+#pragma clang fp contract(off)
   constexpr int D = 128, HALF = 64;
   const int qcols = e.nq * D, kcols = e.nkv * D;
   const int region = n0 < qcols ? 0 : (n0 < qcols + kcols ? 1 : 2);
@@ -219,8 +223,8 @@ __device__ __forceinline__ void acc_qkv(f32x4 (&acc)[RI][CJ], int m0, int M, int
 #pragma unroll
       for (int x = 0; x < CJ / 2; ++x) {
         const f32x4 a = acc[i][2 * x], b = acc[i][2 * x + 1];
-        float s = ((a.x * a.x + a.y * a.y) + (a.z * a.z + a.w * a.w)) +
-                  ((b.x * b.x + b.y * b.y) + (b.z * b.z + b.w * b.w));
+        float s = (fmaf(a.x, a.x, a.y * a.y) + fmaf(a.z, a.z, a.w * a.w)) +
+                  (fmaf(b.x, b.x, b.y * b.y) + fmaf(b.z, b.z, b.w * b.w));
         s += __shfl_xor(s, 16, 64);
         s += __shfl_xor(s, 32, 64);
         if (fq == 0) red[((row(i) - m0) * HT + (hd[x] - ((n0 - rbase) >> 7))) * 4 + (d0[x] >> 4)] = s;
@@ -270,8 +274,8 @@ __device__ __forceinline__ void acc_qkv(f32x4 (&acc)[RI][CJ], int m0, int M, int
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           const float a = acc[i0 + i][2 * x][k], b = acc[i0 + i][2 * x + 1][k];
-          acc[i0 + i][2 * x][k] = a * cc[k] - b * ss[k];
-          acc[i0 + i][2 * x + 1][k] = b * cc[k] + a * ss[k];
+          acc[i0 + i][2 * x][k] = fmaf(a, cc[k], -(b * ss[k]));
+          acc[i0 + i][2 * x + 1][k] = fmaf(b, cc[k], a * ss[k]);
         }
       }
   }

@@ -225,12 +225,13 @@ __global__ __launch_bounds__(NT, 2) void gemm_wide_kernel(GemmParams p, int tile
 
   auto row = [&](int i) { return m0 + (i >> 2) * 128 + wm * 64 + (i & 3) * 16 + fr; };
   auto col = [&](int j) { return (j >> 1) * 128 + wn * 32 + (j & 1) * 16 + 4 * fq; };
-  if (EPI == EPI_QKV) {
+  auto ocol = [&](int j) { return (EPI == EPI_SWIGLU ? tile_n * BN : n0) + col(j); };
+  if constexpr (EPI == EPI_QKV) {
     acc_qkv<8, 4, BM, BN, WAVES, 64>(acc, m0, p.M, n0, p.epi, smem, wave, lane, row, col);
-  } else if (EPI == EPI_RESID) {
-    acc_resid<8, 4, 4>(acc, p.M, p.epi, row, [&](int j) { return n0 + col(j); });
+  } else if constexpr (EPI == EPI_RESID) {
+    acc_resid<8, 4, 4>(acc, p.M, p.epi, row, ocol);
   } else {
-    acc_swiglu<8, 4>(acc, p.M, p.epi, row, [&](int j) { return tile_n * BN + col(j); });
+    acc_swiglu<8, 4>(acc, p.M, p.epi, row, ocol);
   }
 }
 

@@ -80,26 +80,34 @@ void launch_rmsnorm(int dtype, const float* x, const void* gain, void* a_out, in
 int launch_probe(int* dev_flag, hipStream_t s);
 
 // GEMMs with fused epilogues
-void launch_gemm_bf16(int epi, const GemmParams& p, hipStream_t s);
-void launch_gemm_wide(int epi, const GemmParams& p, hipStream_t s);  // EPI_QKV, EPI_RESID, EPI_SWIGLU
+void launch_gemm_bf16(int epi, const GemmParams& p, hipStream_t s);  // picks the tile
+void launch_gemm_wide(int epi, const GemmParams& p, hipStream_t s);  // 256 x 256 tiles: QKV, RESID, SWIGLU
 void launch_gemm_f32(int epi, const GemmParams& p, hipStream_t s);
-// Few-row products (the decode step): K split over enough workgroups to fill
-// the chip, fp32 partials summed in split order by a second kernel that then
-// applies the epilogue `epi`.  part holds part_cap floats.
+// The tiled product as fp32 partial sums of K ranges (EPI_PARTIAL, columns in
+// plain order): tile and K ranges of least cost whose partials fit part_cap
+// floats (one range always counts as fitting).
+struct TilePlan {
+  int tile, ksplit, kt_per;
+};
+TilePlan gemm_tile_split_plan(int M, int N, int K, int64_t part_cap);
+void launch_gemm_tile_partial(const GemmParams& p, const TilePlan& plan, hipStream_t s);
+// Few-row products (the decode step), EPI_QKV and EPI_SWIGLU: K split over
+// enough workgroups to fill the chip, fp32 partials summed in split order by a
+// second kernel that then applies the epilogue; one pass where a split would
+// not pay.  part holds part_cap floats.
 void launch_gemm_bf16_splitk(int epi, const GemmParams& p, float* part, int64_t part_cap,
                              hipStream_t s);
 int64_t gemm_bf16_splitk_part_elems(int M, int N, int K);
 // Few-row product into the residual stream followed by the RMSNorm of the
-// updated rows: X[m] += A[m] . B^T (split-K sums in split order, as
-// launch_gemm_bf16_splitk with EPI_RESID), then a_out[m] = round(gain * X[m] /
-// rms(X[m])) (bf16, row stride N).  Returns false, launching nothing, where
-// the few-row kernel or the row width does not apply.
-bool launch_gemm_bf16_splitk_resid_norm(const GemmParams& p, float* part, int64_t part_cap,
+// updated rows: X[m] += A[m] . B^T (partials summed in split order), then
+// a_out[m] = round(gain * X[m] / rms(X[m])) (bf16, row stride N).  N a multiple
+// of 256, at most 8192.
+void launch_gemm_bf16_splitk_resid_norm(const GemmParams& p, float* part, int64_t part_cap,
                                         const void* gain, void* a_out, float eps, hipStream_t s);
 // Few-row product with K unsplit, fp32 C[M][N] = A . B^T written to out (row
-// stride ldo), no epilogue; B rows follow p.bmap as for the other products.
-// Returns false, launching nothing, unless M <= 64, K % 128 == 0 and N is a
-// multiple of the 16-row blocks a wave owns (64 for M <= 16).
+// stride ldo), no epilogue; plain B rows.  Returns false, launching nothing,
+// unless K % 128 == 0 and N is a multiple of the column blocks used (64 for
+// M <= 16, 32 for M <= 32, 16 for M <= 64, 128 above).
 bool launch_gemm_bf16_rows(const GemmParams& p, float* out, int64_t ldo, hipStream_t s);
 
 // Attention.  qblk: per q-block int4 {q_start, q_len, req_start, 0} in
