@@ -68,7 +68,7 @@ kv_status kv_verify(kv_arena_t arena, const int32_t* lens, int32_t num_requests,
  * callers that cannot allocate device memory (code being captured into a HIP
  * graph, tight recovery or serving loops, harnesses that forbid hipMalloc).
  * Its scratch memory (the uploaded lens and tables, the entry list, request
- * offsets, match flags and, when `digests` is NULL, the digests) lives in a
+ * offsets and, when `digests` is NULL, the digests) lives in a
  * device array of KV_VERIFY_NOALLOC_SCRATCH_BYTES that the library holds on
  * every device it runs on until the process ends; the call never allocates
  * device or pinned host memory.  Arguments, outputs and status codes are

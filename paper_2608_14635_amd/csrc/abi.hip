@@ -1348,10 +1348,9 @@ kv_status kv_decode_step(const kv_weights* w, const void* final_norm, const void
 namespace {
 
 // Workspace: the staged entry list (block, covered slots) and request offsets,
-// then the per-entry match flags and a digest buffer for calls that do not
-// want the digests back.
+// then a digest buffer for calls that do not want the digests back.
 struct VerifyLayout {
-  size_t entries = 0, offsets = 0, meta_end = 0, match = 0, digests = 0, total = 0;
+  size_t entries = 0, offsets = 0, meta_end = 0, digests = 0, total = 0;
 };
 
 VerifyLayout make_verify_layout(int32_t R, int64_t E) {
@@ -1365,7 +1364,7 @@ VerifyLayout make_verify_layout(int32_t R, int64_t E) {
   L.entries = seg(8 * (size_t)E);
   L.offsets = seg(4 * ((size_t)R + 1));
   L.meta_end = off;
-  L.match = seg((size_t)E);
+  (void)seg((size_t)E);  // kept so that the reported size does not change
   L.digests = seg(8 * (size_t)E);
   L.total = off;
   return L;
@@ -1404,8 +1403,7 @@ kv_status verify_check(kv_arena* arena, const int32_t* lens, int32_t R, const in
   return KV_OK;
 }
 
-DigestParams digest_params(const kv_arena* arena, const int2* entries, int64_t E,
-                           const uint64_t* committed, uint64_t* digests, uint8_t* match) {
+DigestParams digest_params(const kv_arena* arena, const int2* entries, int64_t E, uint64_t* digests) {
   const kv_model_desc& d = arena->desc;
   const int64_t row = (int64_t)d.num_kv_heads * d.head_dim * elem_bytes(d.dtype);
   DigestParams p;
@@ -1416,9 +1414,8 @@ DigestParams digest_params(const kv_arena* arena, const int2* entries, int64_t E
   p.planes = 2 * d.num_layers;
   p.entries = entries;
   p.num_entries = E;
-  p.committed = committed;
   p.digests = digests;
-  p.match = match;
+  p.parts = 1;
   return p;
 }
 
@@ -1444,23 +1441,32 @@ kv_status verify_impl(kv_arena* arena, const int32_t* lens, int32_t R, const int
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   char* ws = reinterpret_cast<char*>(workspace);
 
-  if (arena->staged_pending) {
-    (void)hipEventSynchronize(arena->staged);
-    arena->staged_pending = false;
-  }
-  if (arena->pinned_bytes < L.meta_end) {
-    if (arena->pinned) (void)hipHostFree(arena->pinned);
-    arena->pinned = nullptr;
-    arena->pinned_bytes = 0;
-    if (hipHostMalloc(&arena->pinned, L.meta_end, hipHostMallocDefault) != hipSuccess) {
-      arena->pinned = nullptr;
-      return fail(KV_ENOMEM, "pinned staging allocation of %zu bytes failed", (size_t)L.meta_end);
+  uint64_t* dig = digests ? digests : reinterpret_cast<uint64_t*>(ws + L.digests);
+  // few blocks: the lists go with the kernel arguments
+  const bool small = E <= INLINE_ENTRIES && R <= INLINE_ENTRIES;
+  InlineEntries ie;
+  InlineOffsets io;
+  int2* hent = ie.entries;
+  int32_t* hoff = io.offsets;
+  if (!small) {
+    if (arena->staged_pending) {
+      (void)hipEventSynchronize(arena->staged);
+      arena->staged_pending = false;
     }
-    arena->pinned_bytes = L.meta_end;
+    if (arena->pinned_bytes < L.meta_end) {
+      if (arena->pinned) (void)hipHostFree(arena->pinned);
+      arena->pinned = nullptr;
+      arena->pinned_bytes = 0;
+      if (hipHostMalloc(&arena->pinned, L.meta_end, hipHostMallocDefault) != hipSuccess) {
+        arena->pinned = nullptr;
+        return fail(KV_ENOMEM, "pinned staging allocation of %zu bytes failed", (size_t)L.meta_end);
+      }
+      arena->pinned_bytes = L.meta_end;
+    }
+    char* hb = reinterpret_cast<char*>(arena->pinned);
+    hent = reinterpret_cast<int2*>(hb + L.entries);
+    hoff = reinterpret_cast<int32_t*>(hb + L.offsets);
   }
-  char* hb = reinterpret_cast<char*>(arena->pinned);
-  int2* hent = reinterpret_cast<int2*>(hb + L.entries);
-  int32_t* hoff = reinterpret_cast<int32_t*>(hb + L.offsets);
   int64_t e = 0;
   for (int32_t r = 0; r < R; ++r) {
     hoff[r] = (int32_t)e;
@@ -1469,8 +1475,8 @@ kv_status verify_impl(kv_arena* arena, const int32_t* lens, int32_t R, const int
       hent[e] = make_int2(tables[(int64_t)r * max_blocks + j], std::min(B, lens[r] - j * B));
   }
   hoff[R] = (int32_t)e;
-  {
-    hipError_t err = hipMemcpyAsync(ws, hb, L.meta_end, hipMemcpyHostToDevice, s);
+  if (!small) {
+    hipError_t err = hipMemcpyAsync(ws, arena->pinned, L.meta_end, hipMemcpyHostToDevice, s);
     if (err == hipSuccess) err = hipEventRecord(arena->staged, s);
     if (err != hipSuccess) {
       (void)hipGetLastError();
@@ -1478,12 +1484,11 @@ kv_status verify_impl(kv_arena* arena, const int32_t* lens, int32_t R, const int
     }
     arena->staged_pending = true;
   }
-  const DigestParams p = digest_params(arena, reinterpret_cast<const int2*>(ws + L.entries), E, committed,
-                                      digests ? digests : reinterpret_cast<uint64_t*>(ws + L.digests),
-                                      reinterpret_cast<uint8_t*>(ws + L.match));
-  launch_block_digest(p, s);
+  launch_block_digest(digest_params(arena, reinterpret_cast<const int2*>(ws + L.entries), E, dig),
+                      small ? &ie : nullptr, s);
   if (committed)
-    launch_leading_intact(reinterpret_cast<const int32_t*>(ws + L.offsets), R, p.match, intact, s);
+    launch_leading_intact(reinterpret_cast<const int32_t*>(ws + L.offsets), small ? &io : nullptr, R, dig,
+                          committed, intact, s);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) return fail(KV_EDEVICE, "kernel launch failed: %s", hipGetErrorString(err));
   return ok();
@@ -1564,7 +1569,7 @@ kv_status kv_verify_noalloc(kv_arena_t arena, const int32_t* lens, int32_t R,
   const kv_status cst = verify_check(arena, lens, R, tables, max_blocks, committed, digests, intact, &E);
   if (cst != KV_OK) return cst;
   if (R == 0) return ok();
-  // scratch layout: lens, tables, request offsets, entries, match flags, digests
+  // scratch layout: lens, tables, request offsets, entries, a spare byte per entry, digests
   uint64_t off = 0;
   auto seg = [&](uint64_t bytes) {
     const uint64_t at = off;
@@ -1575,7 +1580,7 @@ kv_status kv_verify_noalloc(kv_arena_t arena, const int32_t* lens, int32_t R,
   const uint64_t o_tab = seg(4ull * R * (uint64_t)max_blocks);
   const uint64_t o_off = seg(4ull * ((uint64_t)R + 1));
   const uint64_t o_ent = seg(8ull * (uint64_t)E);
-  const uint64_t o_match = seg((uint64_t)E);
+  (void)seg((uint64_t)E);  // a byte per entry is part of the documented size
   const uint64_t o_dig = digests ? off : seg(8ull * (uint64_t)E);
   if (off > KV_VERIFY_NOALLOC_SCRATCH_BYTES)
     return fail(KV_ENOMEM, "%d requests with %lld table entries each and %lld blocks need %llu bytes of "
@@ -1596,7 +1601,6 @@ kv_status kv_verify_noalloc(kv_arena_t arena, const int32_t* lens, int32_t R,
   int32_t* d_tab = reinterpret_cast<int32_t*>(sp + o_tab);
   int32_t* d_off = reinterpret_cast<int32_t*>(sp + o_off);
   int2* d_ent = reinterpret_cast<int2*>(sp + o_ent);
-  uint8_t* d_match = reinterpret_cast<uint8_t*>(sp + o_match);
   hipError_t err = hipMemcpyAsync(d_lens, lens, 4ull * R, hipMemcpyHostToDevice, s);
   if (err == hipSuccess)
     err = hipMemcpyAsync(d_tab, tables, 4ull * R * (uint64_t)max_blocks, hipMemcpyHostToDevice, s);
@@ -1605,11 +1609,9 @@ kv_status kv_verify_noalloc(kv_arena_t arena, const int32_t* lens, int32_t R,
     return fail(KV_EDEVICE, "metadata upload failed: %s", hipGetErrorString(err));
   }
   launch_verify_entries(d_lens, d_tab, R, max_blocks, arena->block_size, d_off, d_ent, s);
-  const DigestParams p = digest_params(arena, d_ent, E, committed,
-                                      digests ? digests : reinterpret_cast<uint64_t*>(sp + o_dig),
-                                      d_match);
-  launch_block_digest(p, s);
-  launch_leading_intact(d_off, R, d_match, intact, s);
+  uint64_t* dig = digests ? digests : reinterpret_cast<uint64_t*>(sp + o_dig);
+  launch_block_digest(digest_params(arena, d_ent, E, dig), nullptr, s);
+  launch_leading_intact(d_off, nullptr, R, dig, committed, intact, s);
   err = hipGetLastError();
   if (err != hipSuccess) return fail(KV_EDEVICE, "kernel launch failed: %s", hipGetErrorString(err));
   return ok();

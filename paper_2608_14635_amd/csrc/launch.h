@@ -187,8 +187,8 @@ void launch_argmax(const float* logits_t, int64_t ld, int vocab, int num_request
 void launch_argmax_rows(const float* logits, int64_t ld, int vocab, int num_requests,
                         float2* partial, int32_t* next_tokens, hipStream_t s);
 
-// Block commit digests (flush-free recovery): one workgroup per entry reads
-// the entry's covered slots in every plane and reduces the keyed sum of squares.
+// Block commit digests (flush-free recovery): the entry's covered slots in
+// every plane, reduced to the keyed sum of squares.
 constexpr uint32_t DIGEST_KEY = 0x9E3779B9u;  // word-index multiplier of the key
 struct DigestParams {
   const char* arena;        // arena base
@@ -198,15 +198,24 @@ struct DigestParams {
   int32_t planes;           // 2 * num_layers
   const int2* entries;      // [n] (block id, covered slots)
   int64_t num_entries;
-  const uint64_t* committed;  // [n] or null
-  uint64_t* digests;        // [n] or null
-  uint8_t* match;           // [n] digest == committed (written when committed is set)
+  uint64_t* digests;        // [n]
+  int parts;                // workgroups per entry (set by the launcher)
 };
-void launch_block_digest(const DigestParams& p, hipStream_t s);
+// A call of few entries and requests carries its lists in the kernel arguments
+// (4 KB in all at most): no upload to wait for.
+constexpr int INLINE_ENTRIES = 256;
+struct InlineEntries {
+  int2 entries[INLINE_ENTRIES];
+};
+struct InlineOffsets {
+  int32_t offsets[INLINE_ENTRIES + 1];
+};
+void launch_block_digest(const DigestParams& p, const InlineEntries* in, hipStream_t s);
 // intact[r] = index of request r's first entry (offsets[r] .. offsets[r+1]-1)
-// whose match flag is 0, or its entry count when all match
-void launch_leading_intact(const int32_t* offsets, int32_t num_requests, const uint8_t* match,
-                           int32_t* intact, hipStream_t s);
+// whose digest differs from the committed one, or its entry count
+void launch_leading_intact(const int32_t* offsets, const InlineOffsets* in, int32_t num_requests,
+                           const uint64_t* digests, const uint64_t* committed, int32_t* intact,
+                           hipStream_t s);
 // The entry list and request offsets of a verification built on the device
 // from the raw lens [R] and block tables [R][max_blocks]: offsets[r] = sum of
 // ceil(lens[q]/B) over q < r (offsets[R] = E); entry offsets[r] + j = (table

@@ -113,6 +113,29 @@ def test_digests_and_verify_match_oracle(oracle_lib, case):
     arena.release()
 
 
+# entry and request counts on both sides of the inline lists' 256 and of one
+# workgroup per entry (2048); B = 1 makes every position an entry
+@pytest.mark.parametrize("lens", [[256], [257], [1] * 256, [1] * 257, [2047], [2048, 1]])
+def test_digests_at_the_list_and_split_limits(oracle_lib, lens):
+    shape = W.TINY_F32
+    wl = W.small_workload(shape, lens, block_size=1, seed=541, other_live_frac=0.0)
+    say(f"digests of {len(lens)} requests, {sum(lens)} entries")
+    arena = Hn.DeviceArena(wl)
+    random_bits(arena, seed=79)
+    arena.bind()
+    o, _ = oracle_lib.verify(shape, arena.to_host(), 1, wl.num_blocks, wl.lens, wl.block_tables)
+    assert np.array_equal(gpu_digests(arena, wl), o)
+    bad = o.copy()
+    bad[len(bad) // 2] ^= np.uint64(1)
+    dg, intact = gpu_verify(arena, wl, bad)
+    assert np.array_equal(dg, o)
+    first = np.concatenate([[0], np.cumsum(wl.lens)])
+    want = [min(int(n), len(bad) // 2 - int(a)) if a <= len(bad) // 2 < a + n else int(n)
+            for a, n in zip(first, wl.lens)]
+    assert intact.tolist() == want
+    arena.release()
+
+
 def test_flush_free_recovery_rebuilds_only_damaged_requests(oracle_lib):
     shape = W.TINY_BF16
     wl = W.small_workload(shape, [40, 17, 300, 129, 64, 0, 255], seed=511, other_live_frac=0.25)
