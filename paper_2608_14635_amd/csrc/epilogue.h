@@ -1,18 +1,13 @@
-// Fused GEMM epilogues through LDS, for the split-K sums of the decode step and
-// the fp32 GEMM (the tiled bf16 products finish from their accumulators,
-// gemm_epi.h).
+// Epilogues of the decode step's split-K products through LDS (the tiled
+// products finish from their accumulators: gemm_epi.h, gemm_f32.hip).
 //
-// A tile's fp32 accumulators are first parked in LDS as sC[rows][ldc]; the
-// routines below then read it in row-contiguous chunks so that every global
-// store is a full 16-byte (bf16) or 32-byte (fp32) vector:
+// A tile's fp32 sums are first parked in LDS as sC[rows][ldc]; the routines
+// below then read it in row-contiguous chunks so that every global store is a
+// full 16-byte vector:
 //   QKV    : NeoX RoPE on the q and k heads of the tile (pairs (i, i+d/2),
-//            fp32 cos/sin from the per-position table), rounding to the model
-//            dtype, Q rows to the workspace, K and V rows scattered to their
-//            arena slots, and V^T columns for the attention kernel;
-//   RESID  : X += acc on the fp32 residual stream;
-//   STORE  : X = acc (the transposed logits of the decode step's LM head);
-//   SWIGLU : h = silu(gate) * up from the two column halves of the tile (the
-//            split-K path; the one-pass bf16 GEMM forms h from its accumulators).
+//            fp32 cos/sin), rounding to the model dtype, Q rows to the
+//            workspace, K and V rows to their arena slots;
+//   SWIGLU : h = silu(gate) * up from the two column halves of the tile.
 #pragma once
 #include "common.h"
 #include "launch.h"
@@ -109,19 +104,6 @@ __device__ __forceinline__ void epi_qkv(float* sC, int ldc, int rows, int m_base
       } else {
         const int kh = (n0 - qcols) / d + hh;
         const int64_t sl = e.slot[m];
-        if (e.kc != nullptr) {
-          // contiguous per-head copy for attention; padding rows hold zeros so
-          // that keys past a request's end are inert whatever their residual holds
-          const int64_t kr = e.krow != nullptr ? e.krow[m] : m;
-          T* kd = reinterpret_cast<T*>(e.kc) + ((int64_t)kh * e.ldvt + kr) * d;
-          if (sl < 0) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) lo[i] = hi[i] = 0.0f;
-          }
-          store8(kd + c0, lo);
-          store8(kd + c0 + half, hi);
-        }
-        if (sl < 0) continue;  // padding row: nothing goes to the arena
         dst = reinterpret_cast<T*>(e.arena_k) + (sl * e.nkv + kh) * (int64_t)d;
       }
       store8(dst + c0, lo);
@@ -144,7 +126,6 @@ __device__ __forceinline__ void epi_qkv(float* sC, int ldc, int rows, int m_base
       const int m = m_base + r;
       if (m >= M) continue;
       const int64_t sl = e.slot[m];
-      if (sl < 0) continue;  // padding row
       const float* src = sC + (int64_t)r * ldc + c0;
       float v[8];
 #pragma unroll
@@ -153,90 +134,6 @@ __device__ __forceinline__ void epi_qkv(float* sC, int ldc, int rows, int m_base
       T* dst = reinterpret_cast<T*>(e.arena_v) + sl * (int64_t)kcols + col;
       store8(dst, v);
     }
-    if (e.vt != nullptr) {
-      // V^T (col, krow(m)): 8 consecutive rows of one column per item (their key
-      // rows are consecutive and inside one key tile: a request's rows start
-      // on a multiple of 8, and so do its suffix key rows); padding rows get
-      // zeros, so attention reads inert values past a request's last key
-      const int rchunks = rows / 8;
-      for (int it = tid; it < BN * rchunks; it += NT) {
-        const int c = it % BN, rc = it / BN;
-        const int m0 = m_base + rc * 8;
-        if (m0 >= M) continue;
-        const float* src = sC + (int64_t)(rc * 8) * ldc + c;
-        float v[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = e.slot[m0 + i] < 0 ? 0.0f : src[(int64_t)i * ldc];
-        const int64_t kr0 = e.krow != nullptr ? e.krow[m0] : m0;
-        store8(reinterpret_cast<T*>(e.vt) + vt_offset(vbase + c, kr0, e.ldvt, d), v);
-      }
-    }
-  }
-}
-
-// RESID: X += acc on the fp32 residual stream, read and written nontemporally
-// (once per product; it should not evict the operand panels other tiles are
-// streaming through L2).  Loads and stores share one wait counter on this
-// GPU, and once a store is pending every wait for a load becomes a wait for
-// all: so a batch of rows is loaded, summed and only then stored, with no
-// store between a load and its use.  A thread keeps one 4-column chunk; rows
-// are NT/(BN/4) apart.  Tiles cut by M take the plain row-by-row loop.
-template <int BN, int NT>
-__device__ __forceinline__ void epi_resid(const float* sC, int ldc, int rows, int m_base, int M,
-                                          int n0, const EpiParams& e) {
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
-  constexpr int PER_ROW = BN / 4, RSTEP = NT / PER_ROW, RB = 16;
-  const int tid = threadIdx.x;
-  const int c0 = (tid % PER_ROW) * 4, r0 = tid / PER_ROW;
-  if (m_base + rows <= M && rows % (RSTEP * RB) == 0) {
-    for (int rb = 0; rb < rows; rb += RSTEP * RB) {
-      f32x4* xp = reinterpret_cast<f32x4*>(e.x + (int64_t)(m_base + rb + r0) * e.ldx + n0 + c0);
-      const int64_t step = (int64_t)RSTEP * e.ldx / 4;  // f32x4 units between this thread's rows
-      f32x4 xv[RB];
-#pragma unroll
-      for (int b = 0; b < RB; ++b) xv[b] = __builtin_nontemporal_load(xp + b * step);
-#pragma unroll
-      for (int b = 0; b < RB; ++b) {
-        const float* src = sC + (int64_t)(rb + r0 + b * RSTEP) * ldc + c0;
-        xv[b].x += src[0];
-        xv[b].y += src[1];
-        xv[b].z += src[2];
-        xv[b].w += src[3];
-        asm volatile("" : "+v"(xv[b]));  // the sum is formed here, before any store
-      }
-#pragma unroll
-      for (int b = 0; b < RB; ++b) __builtin_nontemporal_store(xv[b], xp + b * step);
-    }
-    return;
-  }
-  for (int it = tid; it < rows * PER_ROW; it += NT) {
-    const int r = it / PER_ROW, c = (it % PER_ROW) * 4;
-    const int m = m_base + r;
-    if (m >= M) continue;
-    f32x4* xp = reinterpret_cast<f32x4*>(e.x + (int64_t)m * e.ldx + n0 + c);
-    const float* src = sC + (int64_t)r * ldc + c;
-    f32x4 xv = __builtin_nontemporal_load(xp);
-    xv.x += src[0];
-    xv.y += src[1];
-    xv.z += src[2];
-    xv.w += src[3];
-    __builtin_nontemporal_store(xv, xp);
-  }
-}
-
-// STORE: X = acc (fp32), columns [n0, n0 + BN) of rows < M.
-template <int BN, int NT>
-__device__ __forceinline__ void epi_store(const float* sC, int ldc, int rows, int m_base, int M,
-                                          int n0, const EpiParams& e) {
-  const int tid = threadIdx.x;
-  const int per_row = BN / 4;
-  for (int it = tid; it < rows * per_row; it += NT) {
-    const int r = it / per_row, c0 = (it % per_row) * 4;
-    const int m = m_base + r;
-    if (m >= M) continue;
-    const float* src = sC + (int64_t)r * ldc + c0;
-    *reinterpret_cast<float4*>(e.x + (int64_t)m * e.ldx + n0 + c0) =
-        make_float4(src[0], src[1], src[2], src[3]);
   }
 }
 

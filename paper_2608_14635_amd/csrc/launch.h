@@ -132,12 +132,13 @@ struct AttnParams {
   int nq, nkv, d;
 };
 // bf16 attention workgroups are 8 waves: HW heads of one GQA group x QW blocks
-// of 32 queries (HW = largest of 8/4/2/1 dividing the group size).
+// of 32 queries (HW = largest of 8/4/2/1 dividing the group size); fp32 ones
+// four waves of 16 queries of one head.
 inline int attn_heads_per_wg(int group) {
   return group % 8 == 0 ? 8 : group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1;
 }
 inline int attn_qblock(int dtype, int group) {
-  return dtype == 1 ? 32 * (8 / attn_heads_per_wg(group)) : 128;
+  return dtype == 1 ? 32 * (8 / attn_heads_per_wg(group)) : 64;
 }
 constexpr int ATTN_QBLOCK_MIN = 32;
 constexpr int ROW_ALIGN = 64;  // each request's rows start on this boundary of the wave
