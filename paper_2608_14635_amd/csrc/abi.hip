@@ -1191,11 +1191,10 @@ kv_status kv_decode_step(const kv_weights* w, const void* final_norm, const void
       launch_gemm_f32(epi, gp, st);
   };
   auto gemm_full = dt == KV_BF16 ? launch_gemm_bf16 : launch_gemm_f32;
-  // a residual product and the RMSNorm of the updated rows with `gain`: one
-  // kernel sums the bf16 partials and norms; fp32 models take them in turn
+  // a residual product and the RMSNorm of the updated rows with `gain`
   auto resid_norm = [&](const GemmParams& gp, const void* gain) {
     if (dt == KV_BF16) {
-      launch_gemm_bf16_splitk_resid_norm(gp, gpart, L.gpart_elems, gain, A, eps, s);
+      launch_gemm_bf16_resid_norm(gp, gpart, L.gpart_elems, gain, A, eps, s);
       return;
     }
     gemm(EPI_RESID, gp, s);

@@ -1,12 +1,12 @@
-// bf16 products of few rows (the resumed decode) on gfx950: a weight-stationary
-// kernel for at most 64 rows, and the split-K partial sums of that kernel and
-// of the tiled one (gemm_tile.hip), finished by kernels that sum the K ranges
-// in a fixed order and apply the decode step's epilogues.  Results are
-// deterministic.
+// bf16 products of the resumed decode on gfx950: a one-pass kernel for at most
+// 64 rows, and, above, the tiled product (gemm_tile.hip) with its split-K
+// partials finished by kernels that sum the K ranges in a fixed order and apply
+// the decode step's epilogues.  Results are deterministic.
 #include <algorithm>
 
 #include "common.h"
 #include "epilogue.h"
+#include "gemm_epi.h"
 #include "launch.h"
 
 namespace kvr {
@@ -15,24 +15,6 @@ namespace {
 
 constexpr int BN = 256;      // columns of an epilogue tile
 constexpr int LDC = BN + 4;  // its fp32 row in LDS, elements
-
-// Weight row of column r of epilogue tile tile_n (gate/up: 128 gate columns,
-// then the same 128 up columns)
-__device__ __forceinline__ const bf16_t* b_row_ptr(const GemmParams& p, int tile_n, int r) {
-  const int64_t K = p.ldb ? p.ldb : p.K;
-  if (p.bmap == BMAP_GATEUP) {
-    const int j = tile_n * (BN / 2) + (r & (BN / 2 - 1));
-    const bf16_t* base = reinterpret_cast<const bf16_t*>(r < BN / 2 ? p.B0 : p.B1);
-    return base + (int64_t)j * K;
-  }
-  const int n = p.n_begin + tile_n * BN + r;
-  if (p.bmap == BMAP_QKV) {
-    if (n < p.s0) return reinterpret_cast<const bf16_t*>(p.B0) + (int64_t)n * K;
-    if (n < p.s1) return reinterpret_cast<const bf16_t*>(p.B1) + (int64_t)(n - p.s0) * K;
-    return reinterpret_cast<const bf16_t*>(p.B2) + (int64_t)(n - p.s1) * K;
-  }
-  return reinterpret_cast<const bf16_t*>(p.B0) + (int64_t)n * K;
-}
 
 // Split-K partials summed in split order (slice 0, then += slice 1, ...),
 // then the fused epilogue, in 32-row x 256-column pieces, exactly as the
@@ -102,63 +84,76 @@ __global__ __launch_bounds__(256) void splitk_epi_kernel(GemmParams p, int tiles
 }
 
 // ---- products of few rows (resumed decode) ----
-// C[M <= 64, N] = A . B^T, weight-stationary: a wave owns NBW blocks of 16
-// output columns (16 weight rows each) and one K range.  It streams those rows
-// once with 16-byte loads (per 128-k chunk a lane takes 64 contiguous bytes of
-// its row) and multiplies them with every row of A on
-// v_mfma_f32_16x16x32_bf16 (16-row tiles of A; rows past M are clamped and
-// their results dropped).  The A fragments of a chunk are loaded once for all
-// NBW blocks: with one block per wave, the A loads (from L2) equal the weight
-// bytes and bound the kernel.  In a chunk of 128 k, MFMA t takes the k values
-// 32t+8q..+7 from lane group q = lane/16 (the matrix core's own operand
-// layout), so each load instruction reads 64 contiguous bytes of each of 16
-// rows and the next one the rest of those lines; the loads are plain (cached),
-// as nontemporal ones would fetch the lines again.  The waves of one K range
-// are consecutive, so a workgroup's waves read the same A lines.  No LDS and
-// no padding work: HBM-bound on the weights.  Output: the fp32 partial sums of
-// the K range, in the split-K partial layout.
-constexpr int SK_CHUNK = 128;   // k per chunk
-constexpr int SK_UNROLL = 2;    // chunks in flight per wave
+// C[M <= 64, N] = A . B^T in one pass: a workgroup of 8 waves owns CB blocks of
+// 16 output columns (16 weight rows each) and each wave an eighth of K.  A wave
+// streams its part of those rows once with 16-byte loads, in the matrix core's
+// own operand layout, SK_UNROLL chunks of 128 k at a time, and multiplies them
+// with every row of A on v_mfma_f32_16x16x32_bf16 (16-row tiles of A; rows past
+// M are clamped and their results dropped).  The waves' sums meet in LDS and are
+// added in wave order, and the epilogue follows in the same kernel: no partial
+// sums in memory, no second launch.
+//
+// HBM-bound on the weights.  A CU can have about 32 KB of loads outstanding
+// (47 GB/s from HBM), shared by the weights and by A's rows from L2, so CB is
+// the smallest that the epilogue allows where that gives every CU a workgroup.
+// The eight K ranges also spread the accesses: all workgroups walking K in step
+// through rows 8 KB apart (hidden size 4096) reach 4.6-4.9 TB/s where other
+// row lengths reach 6.
+constexpr int SK_CHUNK = 128;  // k per chunk
 constexpr int SK_MAX_M = 64;
-// K is split into ranges for about SK_WAVES waves, at most 16 where the
-// epilogue is elementwise (it sums the splits of every output in parallel)
-// and 8 where it works on whole tiles, whose few workgroups read every split
-// (measured best on the 8B shapes with weights not in the last-level cache)
-constexpr int SK_WAVES = 2048, SK_MAX_SPLIT_ELEM = 16, SK_MAX_SPLIT_TILE = 8;
+constexpr int SK_W = 8;        // waves, K ranges
 
-template <int MT, int NBW>
-__global__ __launch_bounds__(256) void gemm_bf16_skinny_kernel(GemmParams p, int ngroups, int kc_per) {
-  const int lane = threadIdx.x & 63;
-  const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (item >= ngroups * p.ksplit) return;  // whole waves
-  const int grp = item % ngroups, split = item / ngroups;
-  const int r16 = lane & 15, q = lane >> 4;
-  const bf16_t* brow[NBW];
-#pragma unroll
-  for (int b = 0; b < NBW; ++b) {
-    const int nb = grp * NBW + b;
-    brow[b] = b_row_ptr(p, nb / (BN / 16), (nb % (BN / 16)) * 16 + r16) + 8 * q;
+// Weight row behind column n of the product, in the order of the epilogue's
+// pairs (QKV: 16 dims and their rotary partners; gate/up: 16 gate and 16 up rows)
+template <int EPI>
+__device__ __forceinline__ const bf16_t* rows_b_ptr(const GemmParams& p, int n) {
+  if (EPI == EPI_SWIGLU)
+    return reinterpret_cast<const bf16_t*>((n >> 4) & 1 ? p.B1 : p.B0) + (int64_t)gateup_perm_row(n) * p.K;
+  if (EPI == EPI_QKV) {
+    const int reg = n < p.s0 ? 0 : n < p.s1 ? p.s0 : p.s1;
+    const void* m = n < p.s0 ? p.B0 : n < p.s1 ? p.B1 : p.B2;
+    return reinterpret_cast<const bf16_t*>(m) + (int64_t)qkv_perm_row(n - reg) * p.K;
   }
+  if (p.bmap == BMAP_QKV) {  // raw columns (a separate pass norms and rotates)
+    if (n < p.s0) return reinterpret_cast<const bf16_t*>(p.B0) + (int64_t)n * p.K;
+    if (n < p.s1) return reinterpret_cast<const bf16_t*>(p.B1) + (int64_t)(n - p.s0) * p.K;
+    return reinterpret_cast<const bf16_t*>(p.B2) + (int64_t)(n - p.s1) * p.K;
+  }
+  return reinterpret_cast<const bf16_t*>(p.B0) + (int64_t)n * p.K;
+}
+
+template <int MT, int CB, int EPI>
+__global__ __launch_bounds__(64 * SK_W) void gemm_rows_kernel(GemmParams p) {
+  // chunks of loads in flight per wave: as many as 256 registers hold
+  constexpr int U = CB * 2 + MT * 2 <= 4 ? 4 : CB + MT <= 3 ? 3 : CB + MT <= 5 ? 2 : 1;
+  constexpr int NP = EPI == EPI_QKV || EPI == EPI_SWIGLU ? CB / 2 : CB;  // column items (pairs or blocks)
+  constexpr int ITEMS = NP * MT * 64;
+  __shared__ __attribute__((aligned(16))) f32x4 red[SK_W][CB * MT * 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r16 = lane & 15, q = lane >> 4;
+  const int n0 = p.n_begin + blockIdx.x * (CB * 16);
+  const bf16_t* brow[CB];
+#pragma unroll
+  for (int b = 0; b < CB; ++b) brow[b] = rows_b_ptr<EPI>(p, n0 + b * 16 + r16) + 8 * q;
   const bf16_t* arow[MT];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt)
     arow[mt] = reinterpret_cast<const bf16_t*>(p.A) + (int64_t)min(mt * 16 + r16, p.M - 1) * p.lda + 8 * q;
   const int KC = p.K / SK_CHUNK;
-  const int kc0 = split * kc_per, kc1 = min(KC, kc0 + kc_per);
-  f32x4 acc[NBW][MT];
+  const int kc0 = wave * KC / SK_W, kc1 = (wave + 1) * KC / SK_W;
+  f32x4 acc[CB][MT];
 #pragma unroll
-  for (int b = 0; b < NBW; ++b)
+  for (int b = 0; b < CB; ++b)
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) acc[b][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  // SK_UNROLL chunks of loads in flight (weights first), then their MFMAs
-  for (int kc = kc0; kc < kc1; kc += SK_UNROLL) {
-    bf16x8 bv[SK_UNROLL][NBW][4], av[SK_UNROLL][MT][4];
+  for (int kc = kc0; kc < kc1; kc += U) {
+    bf16x8 bv[U][CB][4], av[U][MT][4];
 #pragma unroll
-    for (int u = 0; u < SK_UNROLL; ++u) {
+    for (int u = 0; u < U; ++u) {
       if (kc + u < kc1) {
         const int ko = (kc + u) * SK_CHUNK;
 #pragma unroll
-        for (int b = 0; b < NBW; ++b)
+        for (int b = 0; b < CB; ++b)
 #pragma unroll
           for (int t = 0; t < 4; ++t) bv[u][b][t] = *reinterpret_cast<const bf16x8*>(brow[b] + ko + 32 * t);
 #pragma unroll
@@ -168,30 +163,75 @@ __global__ __launch_bounds__(256) void gemm_bf16_skinny_kernel(GemmParams p, int
       }
     }
 #pragma unroll
-    for (int u = 0; u < SK_UNROLL; ++u) {
+    for (int u = 0; u < U; ++u) {
       if (kc + u < kc1) {
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
-          for (int b = 0; b < NBW; ++b)
+          for (int b = 0; b < CB; ++b)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
-              acc[b][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u][mt][t], bv[u][b][t], acc[b][mt], 0, 0, 0);
+              acc[b][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv[u][b][t], av[u][mt][t], acc[b][mt], 0, 0, 0);
       }
     }
   }
-  // a lane holds rows 4q .. 4q+3 of each 16-row tile, at column r16 of a block
+  // lane: columns 4q .. 4q+3 of each block, row r16 of each tile
 #pragma unroll
-  for (int b = 0; b < NBW; ++b) {
-    const int nb = grp * NBW + b;
-    float* out = p.part + split * p.part_stride + nb * 16 + r16;
+  for (int b = 0; b < CB; ++b)
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < MT; ++mt) red[wave][(b * MT + mt) * 64 + lane] = acc[b][mt];
+  __syncthreads();
+  const EpiParams& e = p.epi;
+  for (int it = threadIdx.x; it < ITEMS; it += 64 * SK_W) {
+    const int l = it & 63, mt = (it >> 6) % MT, x = (it >> 6) / MT;
+    const int m = mt * 16 + (l & 15), c4 = 4 * (l >> 4);
+    if (m >= p.M) continue;
+    auto sum = [&](int b) {
+      f32x4 s = red[0][(b * MT + mt) * 64 + l];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int m = mt * 16 + 4 * q + j;
-        if (m < p.M) out[(int64_t)m * p.part_ld] = acc[b][mt][j];
+      for (int w = 1; w < SK_W; ++w) s += red[w][(b * MT + mt) * 64 + l];
+      return s;
+    };
+    if constexpr (EPI == EPI_SWIGLU) {
+      const f32x4 g = sum(2 * x), u = sum(2 * x + 1);
+      float h[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) h[k] = silu(g[k]) * u[k];
+      *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(e.hf) + (int64_t)m * e.ldh + gateup_perm_row(n0 + 32 * x) +
+                                c4) = pack4(h);
+    } else if constexpr (EPI == EPI_QKV) {
+      const f32x4 a = sum(2 * x), b = sum(2 * x + 1);
+      const int n = n0 + 32 * x;
+      const int region = n < p.s0 ? 0 : n < p.s1 ? 1 : 2, c = n - (region == 0 ? 0 : region == 1 ? p.s0 : p.s1);
+      const int hd = c >> 7, d0 = ((c & 127) >> 5) * 16 + c4;
+      float lo[4], hi[4], ba[4] = {0.0f, 0.0f, 0.0f, 0.0f}, bb[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      const bf16_t* bias = reinterpret_cast<const bf16_t*>(region == 0 ? e.bq : region == 1 ? e.bk : e.bv);
+      if (bias != nullptr) {
+        unpack4(*reinterpret_cast<const uint2*>(bias + hd * 128 + d0), ba);
+        unpack4(*reinterpret_cast<const uint2*>(bias + hd * 128 + d0 + 64), bb);
       }
+      const float2* cs = e.rope + (int64_t)e.pos[m] * 64 + d0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float va = a[k] + ba[k], vb = b[k] + bb[k];
+        const float2 t = region < 2 ? cs[k] : make_float2(1.0f, 0.0f);
+        lo[k] = va * t.x - vb * t.y;
+        hi[k] = vb * t.x + va * t.y;
+      }
+      bf16_t* dst;
+      if (region == 0)
+        dst = reinterpret_cast<bf16_t*>(e.q_out) + (int64_t)m * e.nq * 128;
+      else
+        dst = reinterpret_cast<bf16_t*>(region == 1 ? e.arena_k : e.arena_v) + e.slot[m] * (int64_t)(e.nkv * 128);
+      dst += hd * 128 + d0;
+      *reinterpret_cast<uint2*>(dst) = pack4(lo);
+      *reinterpret_cast<uint2*>(dst + 64) = pack4(hi);
+    } else {
+      f32x4* xp = reinterpret_cast<f32x4*>(e.x + (int64_t)m * e.ldx + n0 + x * 16 + c4);
+      f32x4 s = sum(x);
+      if constexpr (EPI == EPI_RESID) s += *xp;
+      *xp = s;
+    }
   }
 }
 
@@ -254,38 +294,16 @@ __global__ __launch_bounds__(RN_THREADS) void splitk_resid_norm_kernel(GemmParam
   }
 }
 
-struct SkinnyPlan {
-  int nbw, ngroups, ksplit, kc_per;
-};
+bool few_rows(int M) { return M > 0 && M <= SK_MAX_M; }
 
-bool skinny_ok(int M, int K) { return M > 0 && M <= SK_MAX_M && K % SK_CHUNK == 0; }
-
-// 16-row blocks per wave: as many as keep the A tiles and the blocks' loads
-// in registers (MT tiles of A cost as much as MT blocks)
-int skinny_nbw(int M) {
-  const int mt = (M + 15) / 16;
-  return mt == 1 ? 4 : mt == 2 ? 2 : 1;
-}
-
-SkinnyPlan skinny_plan(int M, int tiles_n, int K, int max_split) {
-  SkinnyPlan sp;
-  sp.nbw = skinny_nbw(M);
-  sp.ngroups = tiles_n * (BN / 16) / sp.nbw;
-  const int KC = K / SK_CHUNK;
-  const int want = std::max(1, std::min({KC, max_split, SK_WAVES / std::max(1, sp.ngroups)}));
-  sp.kc_per = (KC + want - 1) / want;
-  sp.ksplit = (KC + sp.kc_per - 1) / sp.kc_per;
-  return sp;
-}
-
-// q.ksplit K ranges of kc_per chunks over ngroups groups of 16-row blocks
-void launch_skinny(const GemmParams& q, int ngroups, int kc_per, hipStream_t s) {
-  const dim3 grid((unsigned)((ngroups * q.ksplit + 3) / 4)), block(256);
-  switch ((q.M + 15) / 16) {
-    case 1: hipLaunchKernelGGL((gemm_bf16_skinny_kernel<1, 4>), grid, block, 0, s, q, ngroups, kc_per); break;
-    case 2: hipLaunchKernelGGL((gemm_bf16_skinny_kernel<2, 2>), grid, block, 0, s, q, ngroups, kc_per); break;
-    case 3: hipLaunchKernelGGL((gemm_bf16_skinny_kernel<3, 1>), grid, block, 0, s, q, ngroups, kc_per); break;
-    default: hipLaunchKernelGGL((gemm_bf16_skinny_kernel<4, 1>), grid, block, 0, s, q, ngroups, kc_per); break;
+template <int CB, int EPI>
+void launch_rows(const GemmParams& p, int N, hipStream_t s) {
+  const dim3 grid((unsigned)(N / (16 * CB))), block(64 * SK_W);
+  switch ((p.M + 15) / 16) {
+    case 1: hipLaunchKernelGGL((gemm_rows_kernel<1, CB, EPI>), grid, block, 0, s, p); break;
+    case 2: hipLaunchKernelGGL((gemm_rows_kernel<2, CB, EPI>), grid, block, 0, s, p); break;
+    case 3: hipLaunchKernelGGL((gemm_rows_kernel<3, CB, EPI>), grid, block, 0, s, p); break;
+    default: hipLaunchKernelGGL((gemm_rows_kernel<4, CB, EPI>), grid, block, 0, s, p); break;
   }
 }
 
@@ -296,8 +314,15 @@ int n_tiles_of(const GemmParams& p) {
 }  // namespace
 
 int64_t gemm_bf16_splitk_part_elems(int M, int N, int K) {
-  if (skinny_ok(M, K))  // the larger of the two caps: enough for either epilogue
-    return (int64_t)skinny_plan(M, N / BN, K, SK_MAX_SPLIT_ELEM).ksplit * M * (N / BN) * BN;
+  // few rows: the raw columns of a product whose epilogue is a second pass, in
+  // as many copies as K ranges of 512 up to 16 (the size this has always had)
+  if (few_rows(M)) {
+    const int KC = K / SK_CHUNK, mt = (M + 15) / 16, nbw = mt == 1 ? 4 : mt == 2 ? 2 : 1;
+    const int ngroups = N / 16 / nbw;
+    const int want = std::max(1, std::min({KC, 16, 2048 / std::max(1, ngroups)}));
+    const int per = (KC + want - 1) / want;
+    return (int64_t)((KC + per - 1) / per) * M * (N / BN) * BN;
+  }
   // K ranges that give every CU a 256 x 256 tile; smaller tiles need no more
   const int KT = K / 64, tiles = std::max(1, (M + 255) / 256 * (N / BN));
   const int want = std::max(1, std::min(KT, (256 + tiles - 1) / tiles));
@@ -305,82 +330,84 @@ int64_t gemm_bf16_splitk_part_elems(int M, int N, int K) {
   return (int64_t)((KT + per - 1) / per) * M * (N / BN) * BN;
 }
 
-namespace {
-
-// The K ranges' partial sums of a product of any row count, by the few-row
-// kernel or the tiled one; q.ksplit is set.  one_pass: a plan of one range is
-// not run (returns false).
-bool launch_partials(GemmParams& q, int tiles_n, int max_split, float* part, int64_t part_cap, bool one_pass,
-                     hipStream_t s) {
-  const int64_t ld = (int64_t)tiles_n * BN;
-  q.part = part;
-  q.part_ld = (int)ld;
-  q.part_stride = (int64_t)q.M * ld;
-  if (skinny_ok(q.M, q.K)) {
-    const SkinnyPlan kp = skinny_plan(q.M, tiles_n, q.K, max_split);
-    if ((int64_t)kp.ksplit * q.M * ld <= part_cap) {
-      q.ksplit = kp.ksplit;
-      launch_skinny(q, kp.ngroups, kp.kc_per, s);
-      return true;
-    }
-  }
-  const TilePlan tp = gemm_tile_split_plan(q.M, (int)ld, q.K, part_cap);
-  if (one_pass && tp.ksplit == 1) return false;
-  q.ksplit = tp.ksplit;
-  launch_gemm_tile_partial(q, tp, s);
-  return true;
-}
-
-}  // namespace
-
 void launch_gemm_bf16_splitk(int epi, const GemmParams& p, float* part, int64_t part_cap,
                              hipStream_t s) {
   if (p.M <= 0) return;
-  const int tiles_n = n_tiles_of(p);
+  const int tiles_n = n_tiles_of(p), N = tiles_n * BN;
+  const bool head_norm = epi == EPI_QKV && p.epi.q_norm != nullptr;
   GemmParams q = p;
-  if (!launch_partials(q, tiles_n, SK_MAX_SPLIT_TILE, part, part_cap, true, s)) {
-    launch_gemm_bf16(epi, p, s);
-    return;
+  q.part = part;
+  q.part_ld = N;
+  q.part_stride = (int64_t)p.M * N;
+  q.ksplit = 1;
+  if (few_rows(p.M)) {
+    if (epi == EPI_SWIGLU) {
+      launch_rows<2, EPI_SWIGLU>(p, N, s);
+      return;
+    }
+    if (!head_norm) {
+      launch_rows<2, EPI_QKV>(p, N, s);
+      return;
+    }
+    // per-head norms sum whole heads: the raw columns first
+    q.epi.x = part - p.n_begin;
+    q.epi.ldx = N;
+    launch_rows<1, EPI_STORE>(q, N, s);
+  } else {
+    const TilePlan tp = gemm_tile_split_plan(p.M, N, p.K, part_cap);
+    if (tp.ksplit == 1) {
+      launch_gemm_bf16(epi, p, s);
+      return;
+    }
+    q.ksplit = tp.ksplit;
+    launch_gemm_tile_partial(q, tp, s);
   }
-  const dim3 egrid((unsigned)(((p.M + SK_ROWS - 1) / SK_ROWS) * tiles_n));
+  const unsigned mblocks = (unsigned)((p.M + SK_ROWS - 1) / SK_ROWS);
   if (epi == EPI_QKV) {  // head dim 128: tiles of one head
     const int tiles_h = tiles_n * (BN / 128);
-    const dim3 hgrid((unsigned)(((p.M + SK_ROWS - 1) / SK_ROWS) * tiles_h));
-    hipLaunchKernelGGL((splitk_epi_kernel<EPI_QKV, 128>), hgrid, dim3(256), 0, s, q, tiles_h);
+    hipLaunchKernelGGL((splitk_epi_kernel<EPI_QKV, 128>), dim3(mblocks * tiles_h), dim3(256), 0, s, q, tiles_h);
   } else {
-    hipLaunchKernelGGL((splitk_epi_kernel<EPI_SWIGLU, BN>), egrid, dim3(256), 0, s, q, tiles_n);
+    hipLaunchKernelGGL((splitk_epi_kernel<EPI_SWIGLU, BN>), dim3(mblocks * tiles_n), dim3(256), 0, s, q, tiles_n);
   }
 }
 
-void launch_gemm_bf16_splitk_resid_norm(const GemmParams& p, float* part, int64_t part_cap,
-                                        const void* gain, void* a_out, float eps, hipStream_t s) {
+void launch_gemm_bf16_resid_norm(const GemmParams& p, float* part, int64_t part_cap, const void* gain,
+                                 void* a_out, float eps, hipStream_t s) {
   const int N = p.n_end - p.n_begin;
+  if (few_rows(p.M)) {
+    launch_rows<1, EPI_RESID>(p, N, s);
+    launch_rmsnorm(1, p.epi.x, gain, a_out, p.M, N, eps, s);
+    return;
+  }
   GemmParams q = p;
-  launch_partials(q, N / BN, SK_MAX_SPLIT_ELEM, part, part_cap, false, s);
+  const TilePlan tp = gemm_tile_split_plan(p.M, N, p.K, part_cap);
+  q.part = part;
+  q.part_ld = N;
+  q.part_stride = (int64_t)p.M * N;
+  q.ksplit = tp.ksplit;
+  launch_gemm_tile_partial(q, tp, s);
   hipLaunchKernelGGL(splitk_resid_norm_kernel, dim3((unsigned)p.M), dim3(RN_THREADS), 0, s, q,
                      (const bf16_t*)gain, (bf16_t*)a_out, eps);
 }
 
 bool launch_gemm_bf16_rows(const GemmParams& p, float* out, int64_t ldo, hipStream_t s) {
   const int N = p.n_end - p.n_begin;
-  if (N <= 0 || ldo < N) return false;
-  if (!skinny_ok(p.M, p.K)) {
-    if (N % 128 != 0 || ldo % 4 != 0) return false;
-    GemmParams q = p;
-    q.epi.x = out;
-    q.epi.ldx = (int)ldo;
-    launch_gemm_bf16(EPI_STORE, q, s);
-    return true;
-  }
-  const int nbw = skinny_nbw(p.M);
-  if (N % (16 * nbw) != 0) return false;
+  if (N <= 0 || ldo < N || ldo % 4 != 0 || reinterpret_cast<uintptr_t>(out) % 16 != 0) return false;
   GemmParams q = p;
-  q.part = out;
-  q.part_ld = (int)ldo;
-  q.part_stride = 0;
-  q.ksplit = 1;
-  const int ngroups = N / 16 / nbw, kc_per = p.K / SK_CHUNK;
-  launch_skinny(q, ngroups, kc_per, s);
+  q.epi.x = out;
+  q.epi.ldx = (int)ldo;
+  if (!few_rows(p.M)) {
+    if (N % 128 != 0) return false;
+    launch_gemm_bf16(EPI_STORE, q, s);
+  } else if (N % 64 == 0 && p.M <= 16) {
+    launch_rows<4, EPI_STORE>(q, N, s);
+  } else if (N % 32 == 0) {
+    launch_rows<2, EPI_STORE>(q, N, s);
+  } else if (N % 16 == 0) {
+    launch_rows<1, EPI_STORE>(q, N, s);
+  } else {
+    return false;
+  }
   return true;
 }
 

@@ -91,23 +91,21 @@ struct TilePlan {
 };
 TilePlan gemm_tile_split_plan(int M, int N, int K, int64_t part_cap);
 void launch_gemm_tile_partial(const GemmParams& p, const TilePlan& plan, hipStream_t s);
-// Few-row products (the decode step), EPI_QKV and EPI_SWIGLU: K split over
-// enough workgroups to fill the chip, fp32 partials summed in split order by a
-// second kernel that then applies the epilogue; one pass where a split would
-// not pay.  part holds part_cap floats.
+// Products of a decode step, EPI_QKV and EPI_SWIGLU: one pass for at most 64
+// rows (a second one for per-head norms), above that the tiled product, with
+// fp32 partials of K ranges summed in order by a second kernel where a split
+// pays.  part holds part_cap floats.
 void launch_gemm_bf16_splitk(int epi, const GemmParams& p, float* part, int64_t part_cap,
                              hipStream_t s);
 int64_t gemm_bf16_splitk_part_elems(int M, int N, int K);
-// Few-row product into the residual stream followed by the RMSNorm of the
-// updated rows: X[m] += A[m] . B^T (partials summed in split order), then
-// a_out[m] = round(gain * X[m] / rms(X[m])) (bf16, row stride N).  N a multiple
-// of 256, at most 8192.
-void launch_gemm_bf16_splitk_resid_norm(const GemmParams& p, float* part, int64_t part_cap,
-                                        const void* gain, void* a_out, float eps, hipStream_t s);
-// Few-row product with K unsplit, fp32 C[M][N] = A . B^T written to out (row
-// stride ldo), no epilogue; plain B rows.  Returns false, launching nothing,
-// unless K % 128 == 0 and N is a multiple of the column blocks used (64 for
-// M <= 16, 32 for M <= 32, 16 for M <= 64, 128 above).
+// Product into the residual stream followed by the RMSNorm of the updated
+// rows: X[m] += A[m] . B^T, then a_out[m] = round(gain * X[m] / rms(X[m]))
+// (bf16, row stride N).  N a multiple of 256, at most 8192, = the X row stride.
+void launch_gemm_bf16_resid_norm(const GemmParams& p, float* part, int64_t part_cap, const void* gain,
+                                 void* a_out, float eps, hipStream_t s);
+// fp32 C[M][N] = A . B^T written to out (row stride ldo), no epilogue; plain B
+// rows.  Returns false, launching nothing, unless out is 16-byte aligned,
+// ldo % 4 == 0 and N is a multiple of 16 (of 128 for more than 64 rows).
 bool launch_gemm_bf16_rows(const GemmParams& p, float* out, int64_t ldo, hipStream_t s);
 
 // Attention.  qblk: per q-block int4 {q_start, q_len, req_start, 0} in
