@@ -102,6 +102,7 @@ __global__ __launch_bounds__(256) void splitk_epi_kernel(GemmParams p, int tiles
 constexpr int SK_CHUNK = 128;  // k per chunk
 constexpr int SK_MAX_M = 64;
 constexpr int SK_W = 8;        // waves, K ranges
+constexpr int CUS = 256;
 
 // Weight row behind column n of the product, in the order of the epilogue's
 // pairs (QKV: 16 dims and their rotary partners; gate/up: 16 gate and 16 up rows)
@@ -131,7 +132,10 @@ __global__ __launch_bounds__(64 * SK_W) void gemm_rows_kernel(GemmParams p) {
   __shared__ __attribute__((aligned(16))) f32x4 red[SK_W][CB * MT * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, q = lane >> 4;
-  const int n0 = p.n_begin + blockIdx.x * (CB * 16);
+  // PARTIAL: consecutive workgroups take one K range each of the same columns
+  const int ksplit = EPI == EPI_PARTIAL ? p.ksplit : 1;
+  const int split = EPI == EPI_PARTIAL ? (int)(blockIdx.x % ksplit) : 0;
+  const int n0 = p.n_begin + (EPI == EPI_PARTIAL ? (int)(blockIdx.x / ksplit) : (int)blockIdx.x) * (CB * 16);
   const bf16_t* brow[CB];
 #pragma unroll
   for (int b = 0; b < CB; ++b) brow[b] = rows_b_ptr<EPI>(p, n0 + b * 16 + r16) + 8 * q;
@@ -140,7 +144,8 @@ __global__ __launch_bounds__(64 * SK_W) void gemm_rows_kernel(GemmParams p) {
   for (int mt = 0; mt < MT; ++mt)
     arow[mt] = reinterpret_cast<const bf16_t*>(p.A) + (int64_t)min(mt * 16 + r16, p.M - 1) * p.lda + 8 * q;
   const int KC = p.K / SK_CHUNK;
-  const int kc0 = wave * KC / SK_W, kc1 = (wave + 1) * KC / SK_W;
+  const int range = split * SK_W + wave, ranges = ksplit * SK_W;
+  const int kc0 = range * KC / ranges, kc1 = (range + 1) * KC / ranges;
   f32x4 acc[CB][MT];
 #pragma unroll
   for (int b = 0; b < CB; ++b)
@@ -226,11 +231,10 @@ __global__ __launch_bounds__(64 * SK_W) void gemm_rows_kernel(GemmParams p) {
       dst += hd * 128 + d0;
       *reinterpret_cast<uint2*>(dst) = pack4(lo);
       *reinterpret_cast<uint2*>(dst + 64) = pack4(hi);
+    } else if constexpr (EPI == EPI_PARTIAL) {
+      *reinterpret_cast<f32x4*>(p.part + split * p.part_stride + (int64_t)m * p.part_ld + n0 + x * 16 + c4) = sum(x);
     } else {
-      f32x4* xp = reinterpret_cast<f32x4*>(e.x + (int64_t)m * e.ldx + n0 + x * 16 + c4);
-      f32x4 s = sum(x);
-      if constexpr (EPI == EPI_RESID) s += *xp;
-      *xp = s;
+      *reinterpret_cast<f32x4*>(e.x + (int64_t)m * e.ldx + n0 + x * 16 + c4) = sum(x);
     }
   }
 }
@@ -298,7 +302,7 @@ bool few_rows(int M) { return M > 0 && M <= SK_MAX_M; }
 
 template <int CB, int EPI>
 void launch_rows(const GemmParams& p, int N, hipStream_t s) {
-  const dim3 grid((unsigned)(N / (16 * CB))), block(64 * SK_W);
+  const dim3 grid((unsigned)(N / (16 * CB) * (EPI == EPI_PARTIAL ? p.ksplit : 1))), block(64 * SK_W);
   switch ((p.M + 15) / 16) {
     case 1: hipLaunchKernelGGL((gemm_rows_kernel<1, CB, EPI>), grid, block, 0, s, p); break;
     case 2: hipLaunchKernelGGL((gemm_rows_kernel<2, CB, EPI>), grid, block, 0, s, p); break;
@@ -342,7 +346,12 @@ void launch_gemm_bf16_splitk(int epi, const GemmParams& p, float* part, int64_t 
   q.ksplit = 1;
   if (few_rows(p.M)) {
     if (epi == EPI_SWIGLU) {
-      launch_rows<2, EPI_SWIGLU>(p, N, s);
+      // beyond a few rows A's share of the operand stream outweighs the finer
+      // split (8B, us: 1 row 45.3 / 45.8, 16 rows 55.3 / 50.7, 64 rows 97 / 73)
+      if (p.M <= 4)
+        launch_rows<2, EPI_SWIGLU>(p, N, s);
+      else
+        launch_rows<4, EPI_SWIGLU>(p, N, s);
       return;
     }
     if (!head_norm) {
@@ -374,18 +383,23 @@ void launch_gemm_bf16_splitk(int epi, const GemmParams& p, float* part, int64_t 
 void launch_gemm_bf16_resid_norm(const GemmParams& p, float* part, int64_t part_cap, const void* gain,
                                  void* a_out, float eps, hipStream_t s) {
   const int N = p.n_end - p.n_begin;
-  if (few_rows(p.M)) {
-    launch_rows<1, EPI_RESID>(p, N, s);
-    launch_rmsnorm(1, p.epi.x, gain, a_out, p.M, N, eps, s);
-    return;
-  }
   GemmParams q = p;
-  const TilePlan tp = gemm_tile_split_plan(p.M, N, p.K, part_cap);
   q.part = part;
   q.part_ld = N;
   q.part_stride = (int64_t)p.M * N;
-  q.ksplit = tp.ksplit;
-  launch_gemm_tile_partial(q, tp, s);
+  if (few_rows(p.M)) {
+    // 64 columns a workgroup, so that A is a quarter of the stream (at 16 rows),
+    // and enough K ranges to give every CU one; the norm's kernel adds them up.
+    // (16 columns and all of K in a workgroup, then the norm: 12 us a step more
+    // for one request through 8 layers, 48 for 16 requests through 4.)
+    const int64_t fit = std::max<int64_t>(1, part_cap / q.part_stride);
+    q.ksplit = (int)std::min<int64_t>({(int64_t)std::max(1, CUS / (N / 64)), fit, std::max(1, p.K / SK_CHUNK / SK_W)});
+    launch_rows<4, EPI_PARTIAL>(q, N, s);
+  } else {
+    const TilePlan tp = gemm_tile_split_plan(p.M, N, p.K, part_cap);
+    q.ksplit = tp.ksplit;
+    launch_gemm_tile_partial(q, tp, s);
+  }
   hipLaunchKernelGGL(splitk_resid_norm_kernel, dim3((unsigned)p.M), dim3(RN_THREADS), 0, s, q,
                      (const bf16_t*)gain, (bf16_t*)a_out, eps);
 }
@@ -399,7 +413,7 @@ bool launch_gemm_bf16_rows(const GemmParams& p, float* out, int64_t ldo, hipStre
   if (!few_rows(p.M)) {
     if (N % 128 != 0) return false;
     launch_gemm_bf16(EPI_STORE, q, s);
-  } else if (N % 64 == 0 && p.M <= 16) {
+  } else if (N % 64 == 0) {
     launch_rows<4, EPI_STORE>(q, N, s);
   } else if (N % 32 == 0) {
     launch_rows<2, EPI_STORE>(q, N, s);
