@@ -335,8 +335,7 @@ DecodeLayout make_decode_layout(const kv_model_desc& d, int32_t R, int64_t max_p
   L.R = R;
   L.max_position = max_position;
   L.npad = (int32_t)round_up(std::max<int32_t>(R, 1), 256);
-  // split counts shrink as the batch grows: size for one request's
-  L.splits = decode_attn_splits(1, d.num_kv_heads, max_position);
+  L.splits = decode_attn_max_splits(d.num_kv_heads, max_position);
   if (d.dtype == KV_BF16) {
     const int H = d.hidden, qd = d.num_q_heads * d.head_dim, kvd = d.num_kv_heads * d.head_dim;
     L.gpart_elems = std::max(
@@ -1201,6 +1200,11 @@ kv_status kv_decode_step(const kv_weights* w, const void* final_norm, const void
     launch_rmsnorm(dt, X, gain, A, R, H, eps, s);
   };
 
+  // key ranges of the attention
+  const int chunk = decode_attn_chunk(dt, positions, R, nkv, max_pos + 1);
+  int items = 0;
+  for (int32_t r = 0; r < R; ++r) items += (positions[r] + chunk) / chunk;
+
   // rope rows of the step's positions; the QKV epilogue indexes them by row
   launch_rope_rows(rope, d_pos, R, hd, d.rope_theta, s);
   launch_embed_norm(dt, w->embed, d_tok, w->layers[0].attn_norm, X, A, R, H, eps, s);
@@ -1252,10 +1256,12 @@ kv_status kv_decode_step(const kv_weights* w, const void* final_norm, const void
     ap.nq = nq;
     ap.nkv = nkv;
     ap.d = hd;
-    ap.splits = decode_attn_splits(R, nkv, max_pos + 1);
+    ap.R = R;
+    ap.chunk = chunk;
+    ap.splits = (int)((max_pos + chunk) / chunk);
     ap.part = part;
     ap.out = U;
-    launch_decode_attention(dt, ap, R, s);
+    launch_decode_attention(dt, ap, items, s);
 
     GemmParams go{};
     go.A = U;

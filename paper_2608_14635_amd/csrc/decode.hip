@@ -57,6 +57,32 @@ __device__ __forceinline__ void load_vals8(const bf16_t* p, float* v) {
   v[6] = __uint_as_float(u.w << 16); v[7] = __uint_as_float(u.w & 0xffff0000u);
 }
 
+// Work item j of a step: key range `split` of request r.  Requests have
+// ceil(ctx / chunk) ranges each, numbered request by request; every wave finds
+// its own with a scan over the requests' counts, 64 at a time.
+__device__ __forceinline__ void find_range(const DecodeAttnParams& p, int j, int& r, int& split) {
+  const int lane = threadIdx.x & 63;
+  int base = 0;
+  r = split = 0;
+  for (int r0 = 0; r0 < p.R; r0 += 64) {
+    const int n = r0 + lane < p.R ? (p.ctx[r0 + lane] + p.chunk - 1) / p.chunk : 0;
+    int incl = n;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int v = __shfl_up(incl, o, 64);
+      if (lane >= o) incl += v;
+    }
+    const uint64_t past = __ballot(base + incl > j);
+    if (past != 0) {
+      const int f = __builtin_ctzll(past);
+      r = __builtin_amdgcn_readfirstlane(r0 + f);
+      split = __builtin_amdgcn_readfirstlane(j - base - __shfl(incl - n, f, 64));
+      return;
+    }
+    base += __shfl(incl, 63, 64);
+  }
+}
+
 template <typename T>
 __global__ __launch_bounds__(DNT) void decode_attn_kernel(DecodeAttnParams p) {
   constexpr int PITCH = DMAXD * (int)sizeof(T) + 16;  // bytes per staged row
@@ -67,16 +93,13 @@ __global__ __launch_bounds__(DNT) void decode_attn_kernel(DecodeAttnParams p) {
   __shared__ float s_m[DMAXG], s_l[DMAXG], s_alpha[DMAXG];
   __shared__ int s_tab[TABN];
 
-  const int S = p.splits;
-  int bid = blockIdx.x;
-  const int split = bid % S;
-  bid /= S;
-  const int kvh = bid % p.nkv, r = bid / p.nkv;
+  const int S = p.splits, kvh = blockIdx.x % p.nkv;
+  int r, split;
+  find_range(p, blockIdx.x / p.nkv, r, split);
   const int g = p.nq / p.nkv, d = p.d;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
   const int ctx = p.ctx[r];
-  const int chunk = ((ctx + S - 1) / S + DKB - 1) / DKB * DKB;
-  const int k0 = split * chunk, k1 = min(ctx, k0 + chunk);
+  const int k0 = split * p.chunk, k1 = min(ctx, k0 + p.chunk);
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)d);
   const int64_t row_elems = (int64_t)p.nkv * d;  // one token slot of a plane
 
@@ -235,18 +258,15 @@ __global__ __launch_bounds__(256) void decode_attn_mfma_kernel(DecodeAttnParams 
   __shared__ __attribute__((aligned(16))) float s_p[4][GM * DT];
   __shared__ float s_a[4][16];
   const int S = p.splits, ngrp = (p.nkv + 3) / 4;
-  int bid = blockIdx.x;
-  const int split = bid % S;
-  bid /= S;
-  const int kgrp = bid % ngrp, r = bid / ngrp;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int kvh = kgrp * 4 + wave;
+  const int kvh = (blockIdx.x % ngrp) * 4 + wave;
   if (kvh >= p.nkv) return;  // whole waves
+  int r, split;
+  find_range(p, blockIdx.x / ngrp, r, split);
   const int g = p.nq / p.nkv;
   const int c = lane & 15, q = lane >> 4;
   const int ctx = p.ctx[r];
-  const int chunk = ((ctx + S - 1) / S + DT - 1) / DT * DT;
-  const int k0 = split * chunk, k1 = min(ctx, k0 + chunk);
+  const int k0 = split * p.chunk, k1 = min(ctx, k0 + p.chunk);
   const float scale_log2 = 1.4426950408889634f / sqrtf(128.0f);
   const int64_t row_bytes = (int64_t)p.nkv * 128 * 2;
   const char* Kb = reinterpret_cast<const char*>(p.plane_k) + kvh * 256;
@@ -386,8 +406,8 @@ template <typename T>
 __global__ __launch_bounds__(DMAXD) void decode_combine_kernel(DecodeAttnParams p) {
   __shared__ float s_w[DMAXS], s_red[DMAXD];
   const int r = blockIdx.x / p.nq, h = blockIdx.x % p.nq;
-  const int e = threadIdx.x, d = p.d, S = p.splits, stride = d + 2;
-  const float* base = p.part + ((int64_t)r * p.nq + h) * S * stride;
+  const int e = threadIdx.x, d = p.d, S = (p.ctx[r] + p.chunk - 1) / p.chunk, stride = d + 2;
+  const float* base = p.part + ((int64_t)r * p.nq + h) * p.splits * stride;
   // M: maximum of the splits' m (order-free)
   float mloc = -INFINITY;
   for (int s = e; s < S; s += DMAXD) mloc = fmaxf(mloc, base[s * stride + d]);
@@ -496,15 +516,18 @@ __global__ __launch_bounds__(256) void argmax_partial_kernel(const float* logits
   }
 }
 
-// Pass 1 over row-major logits [R][ld]: workgroup c scans vocabulary chunk c
-// of every request; wave w takes requests w, w+4, ..., its lanes consecutive
-// entries (eight per lane in flight), and merges its lanes with shuffles.
+// Pass 1 over row-major logits [R][ld]: workgroup (c, y) scans vocabulary chunk
+// c of requests 4y .. 4y+3, one per wave, its lanes consecutive entries (eight
+// per lane in flight), and merges its lanes with shuffles.  (With one workgroup
+// per chunk, its waves walking the requests, 100 requests over 152064 entries
+// took 71 us.)
 __global__ __launch_bounds__(256) void argmax_rows_partial_kernel(const float* logits, int64_t ld,
                                                                   int vocab, int R, float2* partial) {
   const int c = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int per = (vocab + ARGMAX_CHUNKS - 1) / ARGMAX_CHUNKS;
   const int v0 = c * per, v1 = min(vocab, v0 + per);
-  for (int r = w; r < R; r += 4) {
+  const int r = blockIdx.y * 4 + w;
+  if (r < R) {
     const float* row = logits + (int64_t)r * ld;
     float best = -INFINITY;
     int bi = -1;
@@ -557,28 +580,43 @@ void launch_rope_rows(float2* table, const int32_t* positions, int rows, int d, 
                      positions, rows, half, theta, d);
 }
 
-int decode_attn_splits(int num_requests, int nkv, int64_t max_ctx) {
-  // enough (request, kv head, key range) items to keep HBM busy (about 2048)
-  // and ranges of at most about 2048 keys, so the longest request's waves
-  // do not trail the rest (measured: 16 requests x 128K context and 64 x
-  // 1.2M both run best at 16 ranges; shorter ranges spend their time on each
-  // wave's fixed costs); at least 64 keys and at most 128 ranges per
-  // (request, kv head).  Never more for more requests, so a workspace sized
-  // for one request's split count fits any larger batch.
-  const int64_t pairs = std::max<int64_t>(1, (int64_t)num_requests * nkv);
-  const int64_t want = std::max<int64_t>((2048 + pairs - 1) / pairs, (max_ctx + 2047) / 2048);
-  const int64_t cap = std::min<int64_t>(DMAXS, (max_ctx + 63) / 64);
-  return (int)std::max<int64_t>(1, std::min(want, cap));
+int decode_attn_max_splits(int nkv, int64_t max_ctx) {
+  const int64_t want = std::max<int64_t>((2048 + nkv - 1) / nkv, (max_ctx + 2047) / 2048);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(want, std::min<int64_t>(DMAXS, (max_ctx + 63) / 64)));
 }
 
-void launch_decode_attention(int dtype, const DecodeAttnParams& p, int num_requests,
-                             hipStream_t s) {
+// The shortest ranges that give at most two workgroups to each of the 256 CUs,
+// so that they all start together and end together: HBM serves 16 requests of
+// equal lengths, two workgroups a CU, at 6.0 TB/s; of 2K to 16K positions in 16
+// ranges each, where the longest request's waves run on alone, at 5.3; in equal
+// ranges of 1.5 / 1.9 / 2.05 / 3 / 4 workgroups a CU a step (4 layers of the 8B
+// shape) took 1302 / 1270 / 1407 / 1366 / 1390 us, with 16 ranges each 1318.  Large batches get half as many again as they have
+// (request, head group) pairs.  At least 64 keys, and no more ranges than the
+// partials hold.
+int decode_attn_chunk(int dtype, const int32_t* positions, int num_requests, int nkv, int64_t max_ctx) {
+  const int64_t per = dtype == 1 ? (nkv + 3) / 4 : nkv;  // workgroups per range
+  const int64_t pairs = num_requests * per;
+  const int64_t target = std::max<int64_t>(512, (pairs + pairs / 2 + 255) / 256 * 256);
+  int64_t total = 0;
+  for (int r = 0; r < num_requests; ++r) total += positions[r] + 1;
+  const int64_t most = decode_attn_max_splits(nkv, max_ctx);
+  int64_t chunk = std::max<int64_t>({total * per / target, (max_ctx + most - 1) / most, 64});
+  chunk = (chunk + 15) / 16 * 16;
+  for (;; chunk += std::max<int64_t>(16, chunk / 64 / 16 * 16)) {
+    int64_t items = 0;
+    for (int r = 0; r < num_requests; ++r) items += (positions[r] + chunk) / chunk;
+    if (items * per <= target || chunk >= max_ctx) return (int)chunk;
+  }
+}
+
+void launch_decode_attention(int dtype, const DecodeAttnParams& p, int items, hipStream_t s) {
+  const int num_requests = p.R;
   if (num_requests <= 0) return;
-  const dim3 grid((unsigned)((int64_t)num_requests * p.nkv * p.splits));
+  const dim3 grid((unsigned)((int64_t)items * p.nkv));
   const dim3 cgrid((unsigned)((int64_t)num_requests * p.nq));
   const int g = p.nq / p.nkv;
   if (dtype == 1 && p.d == 128 && p.block_size % DT == 0 && g <= 16) {
-    const dim3 mgrid((unsigned)((int64_t)num_requests * ((p.nkv + 3) / 4) * p.splits));
+    const dim3 mgrid((unsigned)((int64_t)items * ((p.nkv + 3) / 4)));
     if (g <= 4)
       hipLaunchKernelGGL(decode_attn_mfma_kernel<4>, mgrid, dim3(256), 0, s, p);
     else if (g <= 8)
@@ -607,8 +645,8 @@ void launch_argmax(const float* logits_t, int64_t ld, int vocab, int num_request
 void launch_argmax_rows(const float* logits, int64_t ld, int vocab, int num_requests,
                         float2* partial, int32_t* next_tokens, hipStream_t s) {
   if (num_requests <= 0) return;
-  hipLaunchKernelGGL(argmax_rows_partial_kernel, dim3(ARGMAX_CHUNKS), dim3(256), 0, s, logits, ld,
-                     vocab, num_requests, partial);
+  hipLaunchKernelGGL(argmax_rows_partial_kernel, dim3(ARGMAX_CHUNKS, (num_requests + 3) / 4), dim3(256), 0, s,
+                     logits, ld, vocab, num_requests, partial);
   hipLaunchKernelGGL(argmax_final_kernel, dim3(num_requests), dim3(64), 0, s, partial,
                      num_requests, next_tokens);
 }

@@ -170,15 +170,21 @@ struct DecodeAttnParams {
   const int32_t* tables;  // [R][max_blocks] block tables
   int max_blocks, block_size;
   const int32_t* ctx;     // [R] keys to attend (position + 1)
+  int R;
   int nq, nkv, d;
-  int splits;             // key ranges per (request, kv head)
+  int chunk;              // keys per range, a multiple of 16: request r has ceil(ctx[r] / chunk) ranges
+  int splits;             // ranges of the longest request
   float* part;            // [R][nq][splits][d + 2] partials (o, m, l)
   void* out;              // [R][nq*d] attention output
 };
 void launch_rope_rows(float2* table, const int32_t* positions, int rows, int d, double theta,
                       hipStream_t s);
-int decode_attn_splits(int num_requests, int nkv, int64_t max_ctx);
-void launch_decode_attention(int dtype, const DecodeAttnParams& p, int num_requests, hipStream_t s);
+// Most ranges a request may have (the workspace's partials are sized for it)
+// and the range length of a step: equal ranges for all requests.
+int decode_attn_max_splits(int nkv, int64_t max_ctx);
+int decode_attn_chunk(int dtype, const int32_t* positions, int num_requests, int nkv, int64_t max_ctx);
+// items: ranges of all requests
+void launch_decode_attention(int dtype, const DecodeAttnParams& p, int items, hipStream_t s);
 constexpr int ARGMAX_CHUNKS = 256;  // vocab chunks of the first argmax pass
 void launch_argmax(const float* logits_t, int64_t ld, int vocab, int num_requests,
                    float2* partial, int32_t* next_tokens, float* logits_out, hipStream_t s);

@@ -1,0 +1,80 @@
+"""Decode steps at the edges of their kernels' ranges, against the oracle: more
+requests than one wave of the range scan (64) and than the few-row products (64),
+ragged contexts on both sides of a key range's length, vocabularies that end on
+each column block of the row-major LM head, per-head norms with few rows, and a
+logits buffer that is only 4-byte aligned (the transposed LM head).  Tolerances
+as in test_gpu_decode."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2608_14635_amd import harness as Hn  # noqa: E402
+from paper_2608_14635_amd import kvr  # noqa: E402
+from paper_2608_14635_amd import workloads as W  # noqa: E402
+
+import parity_util as PU  # noqa: E402
+import test_gpu_decode as TD  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+T2 = W.TINY_BF16.with_layers(2)
+CASES = {
+    "130req_ragged": (dataclasses.replace(T2, vocab=1024), [1 + (37 * i) % 701 for i in range(130)], 0),
+    "66req_vocab_128": (dataclasses.replace(T2, vocab=896), [1 + (11 * i) % 90 for i in range(66)], 0),
+    "5req_vocab_16": (dataclasses.replace(T2, vocab=1008), [63, 64, 65, 127, 129], 0),
+    "33req_vocab_32": (dataclasses.replace(T2, vocab=992), [1 + (5 * i) % 140 for i in range(33)], 0),
+    "3req_norm": (dataclasses.replace(T2, vocab=1024, qk_norm=True), [2, 200, 17], 0),
+    "20req_norm_bias": (dataclasses.replace(T2, vocab=1024, qk_norm=True, qkv_bias=True),
+                        [1 + (7 * i) % 60 for i in range(20)], 0),
+    "70req_norm": (dataclasses.replace(T2, vocab=1024, qk_norm=True), [1 + (7 * i) % 60 for i in range(70)], 0),
+    "4req_unaligned_logits": (dataclasses.replace(T2, vocab=1024), [3, 40, 15, 16], 1),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_decode_edges(oracle_lib, name):
+    shape, prefix, shift = CASES[name]
+    tol = PU.TOL[shape.dtype]
+    wl = TD.resume_workload(shape, prefix, steps=2, seed=801)
+    R = len(prefix)
+    TD.say(f"{name}: {R} requests")
+    host_w, head = W.host_weights(shape, seed=802), W.host_head_weights(shape, seed=803)
+    model = Hn.device_model_from_host(shape, host_w)
+    hd = Hn.device_head_from_host(shape, head)
+    image = W.host_arena(wl)
+    # the oracle's own prefixes on both sides
+    pre, last = TD.split_last(wl)
+    ora = image.copy()
+    oracle_lib.rebuild(shape, host_w, pre.tokens, pre.lens, pre.block_tables, ora, wl.block_size, wl.num_blocks)
+    arena = Hn.DeviceArena(wl, host_image=ora)
+    arena.bind()
+    pos = (wl.lens - 1).astype(np.int32)
+    nbytes = kvr.kv_decode_workspace_bytes(shape, R, int(pos.max()) + 1)
+    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
+    nxt = torch.zeros(R, dtype=torch.int32, device="cuda")
+    raw = torch.zeros(R * shape.vocab + 4, dtype=torch.float32, device="cuda")
+    logits = raw[shift:shift + R * shape.vocab]
+    kvr.kv_decode_step(model.weights, hd["final_norm"].data_ptr(), hd["lm_head"].data_ptr(), last, pos,
+                       wl.block_tables, arena.handle, ws.data_ptr(), nbytes, nxt.data_ptr(),
+                       logits.data_ptr(), Hn.stream_ptr())
+    torch.cuda.synchronize()
+    before = ora.copy()
+    fh = oracle_lib.decode_step(shape, host_w, last, pos, wl.block_tables, ora, wl.block_size, wl.num_blocks)
+    want = oracle_lib.logits(shape, head, fh)
+    got = logits.view(R, shape.vocab).cpu().numpy()
+    errs = [TD.rel(got[r], want[r]) for r in range(R)]
+    g = arena.to_host()
+    kv = TD.rel(PU.to_float(TD.slot_rows(wl, g, pos), shape.dtype), PU.to_float(TD.slot_rows(wl, ora, pos), shape.dtype))
+    TD.say(f"  worst logits {max(errs):.2e}, new rows {kv:.2e}")
+    assert max(errs) <= tol and kv <= tol
+    TD.assert_valid_argmax(nxt.cpu().numpy(), want, tol)
+    # nothing but the new slots changed
+    shp = (shape.num_layers, 2, wl.num_blocks, wl.block_size, -1)
+    m = np.zeros(shp[:4], bool)
+    for r, p in enumerate(pos):
+        m[:, :, wl.block_tables[r, p // wl.block_size], p % wl.block_size] = True
+    assert np.array_equal(g.reshape(shp)[~m], before.reshape(shp)[~m])
+    arena.release()
