@@ -223,8 +223,8 @@ __device__ __forceinline__ void acc_qkv(f32x4 (&acc)[RI][CJ], int m0, int M, int
 #pragma unroll
       for (int x = 0; x < CJ / 2; ++x) {
         const f32x4 a = acc[i][2 * x], b = acc[i][2 * x + 1];
-        float s = (fmaf(a.x, a.x, a.y * a.y) + fmaf(a.z, a.z, a.w * a.w)) +
-                  (fmaf(b.x, b.x, b.y * b.y) + fmaf(b.z, b.z, b.w * b.w));
+        float s = ((a.x * a.x + a.y * a.y) + (a.z * a.z + a.w * a.w)) +
+                  ((b.x * b.x + b.y * b.y) + (b.z * b.z + b.w * b.w));
         s += __shfl_xor(s, 16, 64);
         s += __shfl_xor(s, 32, 64);
         if (fq == 0) red[((row(i) - m0) * HT + (hd[x] - ((n0 - rbase) >> 7))) * 4 + (d0[x] >> 4)] = s;
