@@ -300,13 +300,7 @@ void launch_picked(int t, const GemmParams& p, hipStream_t s) {
 
 int columns_of(const GemmParams& p) { return p.bmap == BMAP_GATEUP ? 2 * p.epi.ffn : p.n_end - p.n_begin; }
 
-}  // namespace
-
-void launch_gemm_bf16(int epi, const GemmParams& p, hipStream_t s) {
-  const int N = columns_of(p);
-  if (p.M <= 0 || N <= 0) return;
-  const bool heads = epi == EPI_QKV && p.epi.q_norm != nullptr;
-  const int t = pick_tile(p.M, N, heads, epi != EPI_STORE);
+void launch_one(int t, int epi, const GemmParams& p, hipStream_t s) {
   if (t == T_WIDE) {
     launch_gemm_wide(epi, p, s);
   } else if (epi == EPI_QKV) {
@@ -321,6 +315,63 @@ void launch_gemm_bf16(int epi, const GemmParams& p, hipStream_t s) {
   } else {
     launch_picked<EPI_STORE>(t, p, s);
   }
+}
+
+// Columns [c0, c1) of a product (multiples of 256), as a product of its own
+GemmParams columns(int epi, const GemmParams& p, int c0, int c1) {
+  GemmParams q = p;
+  if (epi == EPI_SWIGLU) {  // half of the columns are outputs
+    q.B0 = reinterpret_cast<const bf16_t*>(p.B0) + (int64_t)(c0 / 2) * p.K;
+    q.B1 = reinterpret_cast<const bf16_t*>(p.B1) + (int64_t)(c0 / 2) * p.K;
+    q.epi.hf = reinterpret_cast<bf16_t*>(p.epi.hf) + c0 / 2;
+    q.epi.ffn = (c1 - c0) / 2;
+  } else {
+    q.n_begin = p.n_begin + c0;
+    q.n_end = p.n_begin + c1;
+  }
+  return q;
+}
+
+}  // namespace
+
+void launch_gemm_bf16(int epi, const GemmParams& p, hipStream_t s) {
+  const int N = columns_of(p);
+  if (p.M <= 0 || N <= 0) return;
+  const bool heads = epi == EPI_QKV && p.epi.q_norm != nullptr, wide_ok = epi != EPI_STORE;
+  const int t = pick_tile(p.M, N, heads, wide_ok);
+  // A last round of workgroups that is mostly empty costs as much as a full
+  // one: where it pays for another launch, whole rounds of one tile take the
+  // first columns and a smaller tile the rest.  Gate/up at 1003 rows, K 4096,
+  // 384 tiles of 256 x 256: 184 us in two rounds, 102 + 71 as one round and one
+  // of 256 x 128 tiles.  Layers of the 8B shape: 520 rows -3.5 %, 3000 -3.2 %,
+  // 4200 -10 %, 9000 -1 %; beyond four rounds there is too little to gain.
+  constexpr int64_t LAUNCH_NS = 8000;
+  const int KT = p.K / BK;
+  const int64_t tiles = tiles_of(t, p.M, N);
+  int64_t cost = tile_cost(t, tiles) * KT * 15 / 16;  // what the costs are good for
+  int best1 = -1, cut = 0;
+  if (wide_ok && tiles > CUS && tiles <= 4 * CUS)
+    for (int t1 = T128x128; t1 < TILES; ++t1) {
+      const int tiles_m = cdiv(p.M, TILE[t1].bm);
+      for (int r = 1; r <= 3; ++r) {
+        const int c = r * CUS / tiles_m * TILE[t1].bn / 256 * 256;  // columns of r whole rounds
+        if (c <= 0 || c >= N) continue;
+        const int t2 = pick_tile(p.M, N - c, heads, wide_ok);
+        const int64_t both = (tile_cost(t1, tiles_of(t1, p.M, c)) + tile_cost(t2, tiles_of(t2, p.M, N - c))) * KT +
+                             LAUNCH_NS;
+        if (both < cost) {
+          cost = both;
+          best1 = t1;
+          cut = c;
+        }
+      }
+    }
+  if (best1 < 0) {
+    launch_one(t, epi, p, s);
+    return;
+  }
+  launch_one(best1, epi, columns(epi, p, 0, cut), s);
+  launch_one(pick_tile(p.M, N - cut, heads, wide_ok), epi, columns(epi, p, cut, N), s);
 }
 
 // Split-K pays where the tiles of a product leave CUs idle: the K tiles per

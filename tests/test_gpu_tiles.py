@@ -61,3 +61,22 @@ def test_a_request_keeps_its_bits_whatever_the_tile(name):
     for r, n in enumerate(LENS):
         assert torch.equal(rows_of(wl, whole, r), rows_of(long, big, r)), f"{n} tokens in the long call"
     sys.stdout.flush()
+
+
+@pytest.mark.parametrize("name", ["llama8b", "qwen3_8b", "qwen25_1_5b"])
+def test_columns_shared_out_over_two_tiles_keep_their_bits(name):
+    """Products whose last round of tiles would be mostly empty take two kinds of
+    tile: q/k/v at 3000 rows (9000 for the 1.5B shape), the residual products at
+    4400 and gate/up at 1003; in one call of all the rows there is one kind."""
+    lens = [1003, 3000, 4400, 9000]
+    shape = W.SHAPES[name].with_layers(2)
+    wl = W.small_workload(shape, lens, seed=613, other_live_frac=0.1)
+    model = Hn.device_model_random(shape, seed=614, gain_std=0.1)
+    whole = rebuild(wl, model)
+    off = wl.request_offsets()
+    for r, n in enumerate(lens):
+        print(f"{name}: {n} tokens alone", flush=True)
+        one = dataclasses.replace(wl, lens=wl.lens[r:r + 1].copy(), tokens=wl.tokens[off[r]:off[r + 1]].copy(),
+                                  block_tables=wl.block_tables[r:r + 1].copy())
+        a, b = rows_of(wl, whole, r), rows_of(one, rebuild(one, model), 0)
+        assert torch.equal(a, b), f"{n} tokens: {(a != b).sum().item()} values differ"
