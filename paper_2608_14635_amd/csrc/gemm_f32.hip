@@ -12,7 +12,7 @@
 // memory.
 //
 // The tiny fp32 decoder's products (384 rows, K 256) are latency-bound: 32 x 32
-// tiles give 96 to 528 workgroups and take 5-6 us each, where 64 x 128 tiles of
+// tiles give 96 to 528 workgroups and take 7-10 us each, where 64 x 128 tiles of
 // scalar loads and vector FMAs took 50-90 us.  Larger batches are bound by the
 // fp32 matrix cores (64 x 64 tiles).
 // Every output is produced by one workgroup in one K order: results do not
