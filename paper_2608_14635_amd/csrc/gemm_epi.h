@@ -42,6 +42,19 @@ __device__ __forceinline__ void unpack4(uint2 u, float* v) {
   v[3] = __uint_as_float(u.y & 0xffff0000u);
 }
 
+// Exchange of two registers between lane groups of 16: odd groups of a with even
+// groups of b, and the upper two groups of a with the lower two of b.
+__device__ __forceinline__ void swap_rows16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap_rows32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+
 // RESID: X += acc (fp32).  GI row frags are loaded, summed and stored at a
 // time; X is touched once per product, so it goes past the caches' reuse.
 template <int RI, int CJ, int GI, typename Row, typename Col>
@@ -102,11 +115,13 @@ __device__ __forceinline__ void acc_swiglu(const f32x4 (&acc)[RI][CJ], int M, co
 // tile's first column (q columns, then k, then v); the tile lies in one of the
 // three regions and starts on a multiple of 32.  smem: the workgroup's LDS
 // (free after the product).  WR: rows of a wave that are consecutive (frags
-// G*WR/16 .. +WR/16-1 for G = 0, 1, ..).  Head dim 128.
-// A head's sum of squares is formed in one fixed order whatever the tile: four
-// dims and their rotary partners per lane, the four lanes of a row, then the
-// head's four 32-column groups pairwise.
-template <int RI, int CJ, int BM, int BN, int WAVES, int WR, typename Row, typename Col>
+// G*WR/16 .. +WR/16-1 for G = 0, 1, ..).  Head dim 128.  NORM: the model has
+// the per-head norms (the tile then holds whole heads); a kernel of its own, as
+// one that decides at run time spills a hundred registers in the 256 x 256 tile.
+// A head's sum of squares is formed in one fixed order whatever the tile: FMAs
+// over 16 dims in index order, then the head's eight such parts pairwise (the
+// order of the split-K epilogue, epilogue.h).
+template <bool NORM, int RI, int CJ, int BM, int BN, int WAVES, int WR, typename Row, typename Col>
 __device__ __forceinline__ void acc_qkv(f32x4 (&acc)[RI][CJ], int m0, int M, int n0, const EpiParams& e,
                                         char* smem, int wave, int lane, Row row, Col col) {
   // every tile's instance has to round alike, so no product is contracted into
@@ -212,23 +227,43 @@ __device__ __forceinline__ void acc_qkv(f32x4 (&acc)[RI][CJ], int m0, int M, int
   int pos[RI];
 #pragma unroll
   for (int i = 0; i < RI; ++i) pos[i] = e.pos[min(row(i), M - 1)];
-  const bf16_t* gain = reinterpret_cast<const bf16_t*>(region == 0 ? e.q_norm : e.k_norm);
-  if (gain != nullptr) {
-    // sum of squares of (row, head): this wave's 32-column groups to LDS
-    float* red = reinterpret_cast<float*>(smem);  // [row][head of the tile][4 groups]
+  if constexpr (NORM) {
+    const bf16_t* gain = reinterpret_cast<const bf16_t*>(region == 0 ? e.q_norm : e.k_norm);
+    // sum of squares of (row, head): eight 16-dim parts, each one chain of FMAs
+    // over its dims in index order, to LDS.  A part's dims lie four to a lane:
+    // the four lanes of a row exchange frags, so that each has one part's whole.
+    float* red = reinterpret_cast<float*>(smem);  // [row][head of the tile][8 parts]
     constexpr int HT = BN / D < 1 ? 1 : BN / D;
     __syncthreads();
+    static_assert(CJ == 4, "four frags for the four lanes of a row");
+    const int pc = n0 + col(fq) - 4 * fq - rbase;  // frag fq's first column in the region
+    const int part = ((pc >> 7) - ((n0 - rbase) >> 7)) * 8 + ((pc >> 4) & 1) * 4 + ((pc & 127) >> 5);
 #pragma unroll
-    for (int i = 0; i < RI; ++i)
+    for (int i = 0; i < RI; ++i) {
+      float t[4][4];  // [frag][dim], after the exchanges [lane of the row][dim]
 #pragma unroll
-      for (int x = 0; x < CJ / 2; ++x) {
-        const f32x4 a = acc[i][2 * x], b = acc[i][2 * x + 1];
-        float s = ((a.x * a.x + a.y * a.y) + (a.z * a.z + a.w * a.w)) +
-                  ((b.x * b.x + b.y * b.y) + (b.z * b.z + b.w * b.w));
-        s += __shfl_xor(s, 16, 64);
-        s += __shfl_xor(s, 32, 64);
-        if (fq == 0) red[((row(i) - m0) * HT + (hd[x] - ((n0 - rbase) >> 7))) * 4 + (d0[x] >> 4)] = s;
+      for (int k = 0; k < 4; ++k) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) t[j][k] = acc[i][j][k];
+        swap_rows16(t[0][k], t[1][k]);
+        swap_rows16(t[2][k], t[3][k]);
+        swap_rows32(t[0][k], t[2][k]);
+        swap_rows32(t[1][k], t[3][k]);
       }
+      float s = 0.0f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s = fmaf(t[q][k], t[q][k], s);
+      red[(row(i) - m0) * HT * 8 + part] = s;
+    }
+    __syncthreads();
+    // one inverse RMS per (row, head), in place of its first part
+    for (int t = wave * 64 + lane; t < BM * HT; t += WAVES * 64) {
+      const f32x4 u = *reinterpret_cast<const f32x4*>(red + t * 8), v = *reinterpret_cast<const f32x4*>(red + t * 8 + 4);
+      const float ss = ((u.x + u.y) + (u.z + u.w)) + ((v.x + v.y) + (v.z + v.w));
+      red[t * 8] = 1.0f / sqrtf(ss / (float)D + e.eps);
+    }
     __syncthreads();
     float ga[CJ / 2][2][4];
 #pragma unroll
@@ -240,9 +275,7 @@ __device__ __forceinline__ void acc_qkv(f32x4 (&acc)[RI][CJ], int m0, int M, int
     for (int i = 0; i < RI; ++i)
 #pragma unroll
       for (int x = 0; x < CJ / 2; ++x) {
-        const f32x4 s = *reinterpret_cast<const f32x4*>(
-            red + ((row(i) - m0) * HT + (hd[x] - ((n0 - rbase) >> 7))) * 4);
-        const float inv = 1.0f / sqrtf(((s.x + s.y) + (s.z + s.w)) / (float)D + e.eps);
+        const float inv = red[((row(i) - m0) * HT + (hd[x] - ((n0 - rbase) >> 7))) * 8];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -275,7 +308,7 @@ __device__ __forceinline__ void acc_qkv(f32x4 (&acc)[RI][CJ], int m0, int M, int
         for (int k = 0; k < 4; ++k) {
           const float a = acc[i0 + i][2 * x][k], b = acc[i0 + i][2 * x + 1][k];
           acc[i0 + i][2 * x][k] = fmaf(a, cc[k], -(b * ss[k]));
-          acc[i0 + i][2 * x + 1][k] = fmaf(b, cc[k], a * ss[k]);
+          acc[i0 + i][2 * x + 1][k] = fmaf(a, ss[k], b * cc[k]);
         }
       }
   }

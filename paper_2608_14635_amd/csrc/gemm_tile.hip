@@ -48,7 +48,7 @@ __device__ __forceinline__ void load_lds(const void* base, int bytes, char* dst,
   __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)dst, 16, voff, soff, 0, 0);
 }
 
-template <int BM, int BN, int WM, int WN, int STAGES, int EPI>
+template <int BM, int BN, int WM, int WN, int STAGES, int EPI, bool NORM = false>
 __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(GemmParams p, int tiles_m, int tiles_n) {
   constexpr int WAVES = WM * WN, WR = BM / WM, WC = BN / WN;  // rows and columns of a wave
   constexpr int RI = WR / 16, CJ = WC / 16;
@@ -221,7 +221,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(GemmParams p, i
   auto col = [&](int j) { return wn * WC + j * 16 + 4 * fq; };
   auto ocol = [&](int j) { return (EPI == EPI_SWIGLU ? tile_n * BN : n0) + col(j); };
   if constexpr (EPI == EPI_QKV) {
-    acc_qkv<RI, CJ, BM, BN, WAVES, WR>(acc, m0, p.M, n0, p.epi, smem, wave, lane, row, col);
+    acc_qkv<NORM, RI, CJ, BM, BN, WAVES, WR>(acc, m0, p.M, n0, p.epi, smem, wave, lane, row, col);
   } else if constexpr (EPI == EPI_RESID) {
     acc_resid<RI, CJ, RI>(acc, p.M, p.epi, row, ocol);
   } else if constexpr (EPI == EPI_SWIGLU) {
@@ -239,7 +239,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(GemmParams p, i
   }
 }
 
-template <int BM, int BN, int WM, int WN, int STAGES, int EPI>
+template <int BM, int BN, int WM, int WN, int STAGES, int EPI, bool NORM = false>
 void launch_tile(const GemmParams& p_in, hipStream_t s) {
   GemmParams p = p_in;
   const int tiles_m = (p.M + BM - 1) / BM;
@@ -247,7 +247,7 @@ void launch_tile(const GemmParams& p_in, hipStream_t s) {
   if (tiles_m <= 0 || tiles_n <= 0) return;
   p.group_m = 8;
   const dim3 grid(tiles_m * tiles_n * (EPI == EPI_PARTIAL ? p.ksplit : 1)), block(64 * WM * WN);
-  hipLaunchKernelGGL((gemm_tile_kernel<BM, BN, WM, WN, STAGES, EPI>), grid, block, 0, s, p, tiles_m, tiles_n);
+  hipLaunchKernelGGL((gemm_tile_kernel<BM, BN, WM, WN, STAGES, EPI, NORM>), grid, block, 0, s, p, tiles_m, tiles_n);
 }
 
 // The tiles, and the time of one K tile with one workgroup on each CU (ns,
@@ -303,11 +303,14 @@ int columns_of(const GemmParams& p) { return p.bmap == BMAP_GATEUP ? 2 * p.epi.f
 void launch_one(int t, int epi, const GemmParams& p, hipStream_t s) {
   if (t == T_WIDE) {
     launch_gemm_wide(epi, p, s);
+  } else if (epi == EPI_QKV && p.epi.q_norm != nullptr) {  // tiles of whole heads
+    switch (t) {
+      case T64x128: launch_tile<64, 128, 2, 2, 6, EPI_QKV, true>(p, s); break;
+      case T256x128: launch_tile<256, 128, 2, 2, 3, EPI_QKV, true>(p, s); break;
+      default: launch_tile<128, 128, 2, 2, 4, EPI_QKV, true>(p, s); break;
+    }
   } else if (epi == EPI_QKV) {
-    if (t == T64x128)
-      launch_tile<64, 128, 2, 2, 6, EPI_QKV>(p, s);
-    else
-      launch_picked<EPI_QKV>(t, p, s);
+    launch_picked<EPI_QKV>(t, p, s);
   } else if (epi == EPI_RESID) {
     launch_picked<EPI_RESID>(t, p, s);
   } else if (epi == EPI_SWIGLU) {

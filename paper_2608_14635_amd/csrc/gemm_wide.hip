@@ -73,7 +73,7 @@ struct Operand {
   int voff[2][2];    // [half][q]: this lane's byte offset for blocks wave + 8q
 };
 
-template <int EPI>
+template <int EPI, bool NORM = false>
 __global__ __launch_bounds__(NT, 2) void gemm_wide_kernel(GemmParams p, int tiles_m, int tiles_n) {
   __shared__ __attribute__((aligned(1024))) char smem[LDS_BYTES];
 
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_wide_kernel(GemmParams p, int tile
   auto col = [&](int j) { return (j >> 1) * 128 + wn * 32 + (j & 1) * 16 + 4 * fq; };
   auto ocol = [&](int j) { return (EPI == EPI_SWIGLU ? tile_n * BN : n0) + col(j); };
   if constexpr (EPI == EPI_QKV) {
-    acc_qkv<8, 4, BM, BN, WAVES, 64>(acc, m0, p.M, n0, p.epi, smem, wave, lane, row, col);
+    acc_qkv<NORM, 8, 4, BM, BN, WAVES, 64>(acc, m0, p.M, n0, p.epi, smem, wave, lane, row, col);
   } else if constexpr (EPI == EPI_RESID) {
     acc_resid<8, 4, 4>(acc, p.M, p.epi, row, ocol);
   } else {
@@ -246,7 +246,9 @@ void launch_gemm_wide(int epi, const GemmParams& p_in, hipStream_t s) {
   // long A panels then stay in the last-level cache), 8 x 4 otherwise
   p.group_m = tiles_n <= 24 ? 4 : 8;
   const dim3 grid(tiles_m * tiles_n), block(NT);
-  if (epi == EPI_QKV)
+  if (epi == EPI_QKV && p.epi.q_norm != nullptr)
+    hipLaunchKernelGGL((gemm_wide_kernel<EPI_QKV, true>), grid, block, 0, s, p, tiles_m, tiles_n);
+  else if (epi == EPI_QKV)
     hipLaunchKernelGGL(gemm_wide_kernel<EPI_QKV>, grid, block, 0, s, p, tiles_m, tiles_n);
   else if (epi == EPI_RESID)
     hipLaunchKernelGGL(gemm_wide_kernel<EPI_RESID>, grid, block, 0, s, p, tiles_m, tiles_n);
