@@ -321,11 +321,14 @@ __global__ __launch_bounds__(NT, 1) void attn_bf16_kernel(AttnParams p) {
 // for the tiny fp32 decoder's 4 x 128 queries; this kernel 13 us.
 constexpr int FKB = 64;  // keys per tile
 
+__device__ __forceinline__ bool finite(float v) { return fabsf(v) < INFINITY; }
+
 template <int HD>
-__global__ __launch_bounds__(256) void attn_f32_kernel(AttnParams p) {
+__global__ __launch_bounds__(256, HD <= 32 ? 4 : HD == 64 ? 3 : 1) void attn_f32_kernel(AttnParams p) {
   constexpr int PITCH = HD + 4, UPR = HD / 4, PF = FKB * UPR / 256, ND = HD / 16;
   __shared__ __attribute__((aligned(16))) float sk[FKB * PITCH];
   __shared__ __attribute__((aligned(16))) float sv[FKB * PITCH];
+  __shared__ __attribute__((aligned(16))) int s_odd[4];  // per wave: it parked a V that is not finite
   const int qb = blockIdx.x / p.nq, h = blockIdx.x % p.nq;
   const int kvh = h / (p.nq / p.nkv);
   const int4 blk = p.qblk[qb];
@@ -375,6 +378,14 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnParams p) {
       *reinterpret_cast<f32x4*>(sk + (idx / UPR) * PITCH + (idx % UPR) * 4) = ka[i];
       *reinterpret_cast<f32x4*>(sv + (idx / UPR) * PITCH + (idx % UPR) * 4) = va[i];
     }
+    bool odd = false;
+    if (kt * FKB + FKB - 1 > pos0) {  // some query does not see all of the tile
+#pragma unroll
+      for (int i = 0; i < PF; ++i)
+        odd = odd || !(finite(va[i].x) && finite(va[i].y) && finite(va[i].z) && finite(va[i].w));
+    }
+    odd = __any(odd);
+    if (lane == 0) s_odd[wid] = odd;
     __syncthreads();
     if (kt + 1 < ntiles) fetch(kt + 1);
     if (wave_active && kt * FKB <= wave_last) {
@@ -421,15 +432,48 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnParams p) {
       for (int t = 0; t < ND; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) o[t][r] *= a;
+      const int4 any = *reinterpret_cast<const int4*>(s_odd);
+      if ((any.x | any.y | any.z | any.w) == 0) {
 #pragma unroll
-      for (int kf = 0; kf < 4; ++kf)
+        for (int kf = 0; kf < 4; ++kf)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const float* vrow = sv + (kf * 16 + 4 * fq + t) * PITCH + fr;
+          for (int t = 0; t < 4; ++t) {
+            const float* vrow = sv + (kf * 16 + 4 * fq + t) * PITCH + fr;
 #pragma unroll
-          for (int dt = 0; dt < ND; ++dt)
-            o[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vrow[dt * 16], s[kf][t], o[dt], 0, 0, 0);
+            for (int dt = 0; dt < ND; ++dt)
+              o[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(vrow[dt * 16], s[kf][t], o[dt], 0, 0, 0);
+          }
+      } else {
+        // A V of the tile is not finite.  A query's probability of a key it
+        // does not see is 0, but 0 times such a value is not: the products run
+        // without those values, and each query adds the ones it sees.
+#pragma unroll
+        for (int kf = 0; kf < 4; ++kf)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            const float* vrow = sv + (kf * 16 + 4 * fq + t) * PITCH + fr;
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt)
+              o[dt] = __builtin_amdgcn_mfma_f32_16x16x4f32(finite(vrow[dt * 16]) ? vrow[dt * 16] : 0.0f, s[kf][t],
+                                                           o[dt], 0, 0, 0);
+          }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+#pragma unroll 1
+          for (int g = 0; g < 4; ++g) {
+            const int j = (i >> 2) * 16 + 4 * g + (i & 3);
+            const float w = __shfl(s[i >> 2][i & 3], g * 16 + fr, 64);
+            if (kt * FKB + j > qpos) continue;
+#pragma unroll
+            for (int dt = 0; dt < ND; ++dt)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const float v = sv[j * PITCH + dt * 16 + 4 * fq + r];
+                if (!finite(v)) o[dt][r] = fmaf(w, v, o[dt][r]);
+              }
+          }
         }
+      }
     }
     __syncthreads();
   }

@@ -75,3 +75,44 @@ def test_f32_large_tiles_keep_the_bits():
             p = np.arange(int(wl.lens[r]))
             blk, sl = wl.block_tables[r, p // wl.block_size], p % wl.block_size
             assert np.array_equal(whole[:, :, blk, sl], alone[:, :, blk, sl]), (s.head_dim, r)
+
+
+def poisoned(shape, host_w, kind):
+    """Token 0's row, made to give a layer-0 K and V of NaN, or a V of infinities
+    over a finite K: hidden dim 0 is token 0's own, and Wv's column of it is huge."""
+    host_w["embed"][:, 0] = 0.0
+    host_w["embed"][0, 0] = np.inf if kind == "nan" else 1.0
+    if kind == "inf_v":
+        host_w["layers"][0]["wv"][:, 0] = 3e38
+
+
+# the poisoned token on both sides of the edges of the 16-key pieces and the 64-key
+# tiles, in a request that ends inside one
+@pytest.mark.parametrize("kind", ["nan", "inf_v"])
+@pytest.mark.parametrize("name", ["d16", "d64_norm_bias", "d128"])
+def test_f32_later_keys_that_are_not_finite(oracle_lib, name, kind):
+    """Earlier positions keep their bits whatever a later key's values are, and the
+    rows that are not finite are the oracle's."""
+    shape, n = SHAPES[name], 141
+    wl = W.small_workload(shape, [n], seed=731, other_live_frac=0.0)
+    wl.tokens[wl.tokens == 0] = 1
+    host_w = W.host_weights(shape, seed=732)
+    poisoned(shape, host_w, kind)
+    model = Hn.device_model_from_host(shape, host_w)
+    image = W.host_arena(wl)
+    p = np.arange(n)
+    shp = (shape.num_layers, 2, wl.num_blocks, wl.block_size, -1)
+    rows = lambda a: PU.to_float(a.reshape(shp)[:, :, wl.block_tables[0, p // wl.block_size], p % wl.block_size], W.F32)
+    clean = rows(rebuild(wl, model, image))
+    assert np.isfinite(clean).all()
+    for t in (0, 1, 15, 16, 40, 63, 64, 79, 127, 128, 140):
+        print(f"{name} {kind}: position {t}", flush=True)
+        bad = dataclasses.replace(wl, tokens=wl.tokens.copy())
+        bad.tokens[t] = 0
+        got = rows(rebuild(bad, model, image))
+        want = image.copy()
+        oracle_lib.rebuild(shape, host_w, bad.tokens, bad.lens, bad.block_tables, want, bad.block_size, bad.num_blocks)
+        want = rows(want)
+        assert np.array_equal(got[:, :, :t].view(np.uint32), clean[:, :, :t].view(np.uint32))
+        assert np.array_equal(np.isfinite(got), np.isfinite(want))
+        assert not np.isfinite(got[1, :, t + 1:]).any()
