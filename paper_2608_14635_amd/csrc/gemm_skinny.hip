@@ -220,8 +220,9 @@ __global__ __launch_bounds__(64 * SK_W) void gemm_rows_kernel(GemmParams p) {
       for (int k = 0; k < 4; ++k) {
         const float va = a[k] + ba[k], vb = b[k] + bb[k];
         const float2 t = region < 2 ? cs[k] : make_float2(1.0f, 0.0f);
-        lo[k] = va * t.x - vb * t.y;
-        hi[k] = vb * t.x + va * t.y;
+        // a v dim has no partner (and 0 times one that is not finite is not 0)
+        lo[k] = region < 2 ? va * t.x - vb * t.y : va;
+        hi[k] = region < 2 ? vb * t.x + va * t.y : vb;
       }
       bf16_t* dst;
       if (region == 0)

@@ -78,3 +78,32 @@ def test_decode_edges(oracle_lib, name):
         m[:, :, wl.block_tables[r, p // wl.block_size], p % wl.block_size] = True
     assert np.array_equal(g.reshape(shp)[~m], before.reshape(shp)[~m])
     arena.release()
+
+
+@pytest.mark.parametrize("R", [1, 20, 64, 65])
+def test_decode_v_that_is_not_finite_stays_in_its_dim(oracle_lib, R):
+    """V has no rotary partners: an infinite and a NaN bias reach their own dims of
+    the new V rows and no others."""
+    shape = dataclasses.replace(T2, num_layers=1, vocab=1024, qkv_bias=True)
+    wl = TD.resume_workload(shape, [1 + (3 * i) % 20 for i in range(R)], steps=2, seed=811)
+    TD.say(f"{R} requests, value biases that are not finite")
+    host_w, head = W.host_weights(shape, seed=812), W.host_head_weights(shape, seed=813)
+    bv = host_w["layers"][0]["bv"]
+    bv[3], bv[128 + 100] = 0x7F80, 0x7FC0
+    model = Hn.device_model_from_host(shape, host_w)
+    hd = Hn.device_head_from_host(shape, head)
+    image = np.zeros_like(W.host_arena(wl))
+    arena = Hn.DeviceArena(wl, host_image=image)
+    arena.bind()
+    pos = (wl.lens - 1).astype(np.int32)
+    tok = np.arange(R, dtype=np.int32) % shape.vocab
+    GD = TD.GpuDecoder(wl, model, hd, int(pos.max()) + 1)
+    GD.step(arena, tok, pos)
+    g = PU.to_float(TD.slot_rows(wl, arena.to_host(), pos), W.BF16)
+    arena.release()
+    oracle_lib.decode_step(shape, host_w, tok, pos, wl.block_tables, image, wl.block_size, wl.num_blocks)
+    o = PU.to_float(TD.slot_rows(wl, image, pos), W.BF16)
+    assert np.array_equal(np.isfinite(g), np.isfinite(o)) and (~np.isfinite(g)).sum() == 2 * R
+    assert (g[0, 1, :, 3] == np.inf).all() and np.isnan(g[0, 1, :, 228]).all()
+    ok = np.isfinite(o)
+    assert TD.rel(g[ok], o[ok]) <= PU.TOL[W.BF16]
