@@ -58,8 +58,7 @@ kv_status kv_block_digests(kv_arena_t arena, const int32_t* lens, int32_t num_re
  * uint64 [E], may be NULL) and, per request, the number of its leading blocks
  * whose digest equals the committed one to intact (device int32
  * [num_requests]); request r survived intact when intact[r] equals its block
- * count.  digests may be committed itself: the counts are against the records as
- * they were before the call.  Same status codes as kv_block_digests. */
+ * count.  Same status codes as kv_block_digests. */
 kv_status kv_verify(kv_arena_t arena, const int32_t* lens, int32_t num_requests,
                     const int32_t* block_tables, int32_t max_blocks_per_req,
                     const uint64_t* committed, void* workspace, uint64_t workspace_bytes,
@@ -69,7 +68,7 @@ kv_status kv_verify(kv_arena_t arena, const int32_t* lens, int32_t num_requests,
  * callers that cannot allocate device memory (code being captured into a HIP
  * graph, tight recovery or serving loops, harnesses that forbid hipMalloc).
  * Its scratch memory (the uploaded lens and tables, the entry list, request
- * offsets, match flags and, when `digests` is NULL, the digests) lives in a
+ * offsets and, when `digests` is NULL, the digests) lives in a
  * device array of KV_VERIFY_NOALLOC_SCRATCH_BYTES that the library holds on
  * every device it runs on until the process ends; the call never allocates
  * device or pinned host memory.  Arguments, outputs and status codes are

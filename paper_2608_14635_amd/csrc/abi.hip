@@ -1353,10 +1353,9 @@ kv_status kv_decode_step(const kv_weights* w, const void* final_norm, const void
 namespace {
 
 // Workspace: the staged entry list (block, covered slots) and request offsets,
-// then match flags (for digests that overwrite the committed ones) and a digest
-// buffer for calls that do not want the digests back.
+// then a digest buffer for calls that do not want the digests back.
 struct VerifyLayout {
-  size_t entries = 0, offsets = 0, meta_end = 0, match = 0, digests = 0, total = 0;
+  size_t entries = 0, offsets = 0, meta_end = 0, digests = 0, total = 0;
 };
 
 VerifyLayout make_verify_layout(int32_t R, int64_t E) {
@@ -1370,7 +1369,7 @@ VerifyLayout make_verify_layout(int32_t R, int64_t E) {
   L.entries = seg(8 * (size_t)E);
   L.offsets = seg(4 * ((size_t)R + 1));
   L.meta_end = off;
-  L.match = seg((size_t)E);
+  (void)seg((size_t)E);  // kept so that the reported size does not change
   L.digests = seg(8 * (size_t)E);
   L.total = off;
   return L;
@@ -1409,10 +1408,7 @@ kv_status verify_check(kv_arena* arena, const int32_t* lens, int32_t R, const in
   return KV_OK;
 }
 
-// Digests written over the committed ones are compared entry by entry before they
-// are stored (match, [E] bytes); otherwise the intact counts compare the two lists.
-DigestParams digest_params(const kv_arena* arena, const int2* entries, int64_t E, const uint64_t* committed,
-                           uint64_t* digests, uint8_t* match) {
+DigestParams digest_params(const kv_arena* arena, const int2* entries, int64_t E, uint64_t* digests) {
   const kv_model_desc& d = arena->desc;
   const int64_t row = (int64_t)d.num_kv_heads * d.head_dim * elem_bytes(d.dtype);
   DigestParams p;
@@ -1424,9 +1420,6 @@ DigestParams digest_params(const kv_arena* arena, const int2* entries, int64_t E
   p.entries = entries;
   p.num_entries = E;
   p.digests = digests;
-  p.committed = committed;
-  const bool overlap = committed && committed < digests + E && digests < committed + E;
-  p.match = overlap ? match : nullptr;
   p.parts = 1;
   return p;
 }
@@ -1496,12 +1489,11 @@ kv_status verify_impl(kv_arena* arena, const int32_t* lens, int32_t R, const int
     }
     arena->staged_pending = true;
   }
-  const DigestParams p = digest_params(arena, reinterpret_cast<const int2*>(ws + L.entries), E, committed, dig,
-                                       reinterpret_cast<uint8_t*>(ws + L.match));
-  launch_block_digest(p, small ? &ie : nullptr, s);
+  launch_block_digest(digest_params(arena, reinterpret_cast<const int2*>(ws + L.entries), E, dig),
+                      small ? &ie : nullptr, s);
   if (committed)
     launch_leading_intact(reinterpret_cast<const int32_t*>(ws + L.offsets), small ? &io : nullptr, R, dig,
-                          committed, p.match, intact, s);
+                          committed, intact, s);
   const hipError_t err = hipGetLastError();
   if (err != hipSuccess) return fail(KV_EDEVICE, "kernel launch failed: %s", hipGetErrorString(err));
   return ok();
@@ -1582,7 +1574,7 @@ kv_status kv_verify_noalloc(kv_arena_t arena, const int32_t* lens, int32_t R,
   const kv_status cst = verify_check(arena, lens, R, tables, max_blocks, committed, digests, intact, &E);
   if (cst != KV_OK) return cst;
   if (R == 0) return ok();
-  // scratch layout: lens, tables, request offsets, entries, match flags, digests
+  // scratch layout: lens, tables, request offsets, entries, a spare byte per entry, digests
   uint64_t off = 0;
   auto seg = [&](uint64_t bytes) {
     const uint64_t at = off;
@@ -1593,7 +1585,7 @@ kv_status kv_verify_noalloc(kv_arena_t arena, const int32_t* lens, int32_t R,
   const uint64_t o_tab = seg(4ull * R * (uint64_t)max_blocks);
   const uint64_t o_off = seg(4ull * ((uint64_t)R + 1));
   const uint64_t o_ent = seg(8ull * (uint64_t)E);
-  const uint64_t o_match = seg((uint64_t)E);
+  (void)seg((uint64_t)E);  // a byte per entry is part of the documented size
   const uint64_t o_dig = digests ? off : seg(8ull * (uint64_t)E);
   if (off > KV_VERIFY_NOALLOC_SCRATCH_BYTES)
     return fail(KV_ENOMEM, "%d requests with %lld table entries each and %lld blocks need %llu bytes of "
@@ -1623,9 +1615,8 @@ kv_status kv_verify_noalloc(kv_arena_t arena, const int32_t* lens, int32_t R,
   }
   launch_verify_entries(d_lens, d_tab, R, max_blocks, arena->block_size, d_off, d_ent, s);
   uint64_t* dig = digests ? digests : reinterpret_cast<uint64_t*>(sp + o_dig);
-  const DigestParams p = digest_params(arena, d_ent, E, committed, dig, reinterpret_cast<uint8_t*>(sp + o_match));
-  launch_block_digest(p, nullptr, s);
-  launch_leading_intact(d_off, nullptr, R, dig, committed, p.match, intact, s);
+  launch_block_digest(digest_params(arena, d_ent, E, dig), nullptr, s);
+  launch_leading_intact(d_off, nullptr, R, dig, committed, intact, s);
   err = hipGetLastError();
   if (err != hipSuccess) return fail(KV_EDEVICE, "kernel launch failed: %s", hipGetErrorString(err));
   return ok();

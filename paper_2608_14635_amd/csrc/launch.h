@@ -204,8 +204,6 @@ struct DigestParams {
   const int2* entries;      // [n] (block id, covered slots)
   int64_t num_entries;
   uint64_t* digests;        // [n]
-  const uint64_t* committed;  // [n], with match: the records to compare with
-  uint8_t* match;           // [n] digest == committed, or null
   int parts;                // workgroups per entry (set by the launcher)
 };
 // A call of few entries and requests carries its lists in the kernel arguments
@@ -219,11 +217,10 @@ struct InlineOffsets {
 };
 void launch_block_digest(const DigestParams& p, const InlineEntries* in, hipStream_t s);
 // intact[r] = index of request r's first entry (offsets[r] .. offsets[r+1]-1)
-// whose digest differs from the committed one (match[e] == 0 where match is
-// given), or its entry count
+// whose digest differs from the committed one, or its entry count
 void launch_leading_intact(const int32_t* offsets, const InlineOffsets* in, int32_t num_requests,
-                           const uint64_t* digests, const uint64_t* committed, const uint8_t* match,
-                           int32_t* intact, hipStream_t s);
+                           const uint64_t* digests, const uint64_t* committed, int32_t* intact,
+                           hipStream_t s);
 // The entry list and request offsets of a verification built on the device
 // from the raw lens [R] and block tables [R][max_blocks]: offsets[r] = sum of
 // ceil(lens[q]/B) over q < r (offsets[R] = E); entry offsets[r] + j = (table

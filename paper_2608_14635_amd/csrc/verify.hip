@@ -74,7 +74,6 @@ __global__ __launch_bounds__(DG_THREADS) void block_digest_kernel(DigestParams p
     __syncthreads();
   }
   if (t == 0) {
-    if (p.match) p.match[e] = red[0] == p.committed[e];  // before the store: the two may be one buffer
     if (p.parts == 1)
       p.digests[e] = red[0];
     else  // a sum modulo 2^64: exact in any order
@@ -92,7 +91,7 @@ __global__ __launch_bounds__(DG_THREADS) void leading_intact_kernel(const int32_
                                                                     InlineOffsets in,
                                                                     const uint64_t* digests,
                                                                     const uint64_t* committed,
-                                                                    const uint8_t* match, int32_t* intact) {
+                                                                    int32_t* intact) {
   __shared__ int32_t red[DG_THREADS];
   const int r = blockIdx.x;
   const int32_t off = INL ? in.offsets[r] : offsets[r];
@@ -101,7 +100,7 @@ __global__ __launch_bounds__(DG_THREADS) void leading_intact_kernel(const int32_
   int32_t first = nb;
   // the first mismatch among entries t, t+256, ...; the minimum over lanes is the first overall
   for (int32_t j = t; j < nb; j += DG_THREADS)
-    if (match ? !match[off + j] : digests[off + j] != committed[off + j]) {
+    if (digests[off + j] != committed[off + j]) {
       first = j;
       break;
     }
@@ -172,8 +171,7 @@ void launch_block_digest(const DigestParams& p_in, const InlineEntries* in, hipS
   // of workgroups (fewer than two a CU) and one workgroup would take longer over
   // an entry (about 47 GB/s) than the clearing launch costs (4 us).  Without
   // the first line about a thousand entries took 29.5 instead of 25.2 us.
-  // (Match flags come from the one workgroup that has the entry's whole sum.)
-  const bool few = !p.match && p.num_entries < 512 && (int64_t)p.planes * p.block_bytes >= (256 << 10);
+  const bool few = p.num_entries < 512 && (int64_t)p.planes * p.block_bytes >= (256 << 10);
   p.parts = few ? (int)std::min<int64_t>(p.planes, (2048 + p.num_entries - 1) / p.num_entries) : 1;
   if (p.parts > 1)
     clear_digests_kernel<<<dim3((unsigned)((p.num_entries + DG_THREADS - 1) / DG_THREADS)), dim3(DG_THREADS), 0,
@@ -186,15 +184,15 @@ void launch_block_digest(const DigestParams& p_in, const InlineEntries* in, hipS
 }
 
 void launch_leading_intact(const int32_t* offsets, const InlineOffsets* in, int32_t num_requests,
-                           const uint64_t* digests, const uint64_t* committed, const uint8_t* match,
-                           int32_t* intact, hipStream_t s) {
+                           const uint64_t* digests, const uint64_t* committed, int32_t* intact,
+                           hipStream_t s) {
   if (num_requests <= 0) return;
   if (in)
     leading_intact_kernel<true><<<dim3((unsigned)num_requests), dim3(DG_THREADS), 0, s>>>(offsets, *in, digests,
-                                                                                          committed, match, intact);
+                                                                                          committed, intact);
   else
     leading_intact_kernel<false><<<dim3((unsigned)num_requests), dim3(DG_THREADS), 0, s>>>(
-        offsets, InlineOffsets{}, digests, committed, match, intact);
+        offsets, InlineOffsets{}, digests, committed, intact);
 }
 
 }  // namespace kvr

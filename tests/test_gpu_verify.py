@@ -136,40 +136,6 @@ def test_digests_at_the_list_and_split_limits(oracle_lib, lens):
     arena.release()
 
 
-# small entries, and entries large enough that a call of few of them shares their
-# planes out; with and without the lists in the kernel arguments
-@pytest.mark.parametrize("call", ["verify", "noalloc"])
-@pytest.mark.parametrize("shape,lens", [(W.TINY_F32, [50, 0, 200]), (W.LLAMA8B.with_layers(5), [50, 0, 200]),
-                                        (W.TINY_F32, [5000, 33])], ids=["small", "shared", "many"])
-def test_digests_written_over_the_committed_ones(oracle_lib, shape, lens, call):
-    """committed and digests may be one buffer: the counts are against what it held."""
-    wl = W.small_workload(shape, lens, seed=551, other_live_frac=0.0)
-    B, E = wl.block_size, kvr.num_entries(wl.lens, wl.block_size)
-    say(f"{call} over its records: {E} entries")
-    arena = Hn.DeviceArena(wl)
-    random_bits(arena, seed=83)
-    arena.bind()
-    o, _ = oracle_lib.verify(shape, arena.to_host(), B, wl.num_blocks, wl.lens, wl.block_tables)
-    old = o.copy()
-    old[[2, E - 1]] ^= np.uint64(1 << 40)
-    both = torch.from_numpy(old.view(np.int64).copy()).cuda()
-    intact = torch.full((len(lens),), -5, dtype=torch.int32, device="cuda")
-    if call == "verify":
-        nbytes = kvr.kv_verify_workspace_bytes(len(lens), E)
-        ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
-        kvr.kv_verify(arena.handle, wl.lens, wl.block_tables, both.data_ptr(), ws.data_ptr(), nbytes,
-                      intact.data_ptr(), both.data_ptr(), Hn.stream_ptr())
-    else:
-        kvr.kv_verify_noalloc(arena.handle, wl.lens, wl.block_tables, both.data_ptr(), intact.data_ptr(),
-                              both.data_ptr(), Hn.stream_ptr())
-    torch.cuda.synchronize()
-    arena.release()
-    assert np.array_equal(both.cpu().numpy().view(np.uint64), o)
-    nb = (wl.lens + B - 1) // B
-    nb[0], nb[-1] = 2, nb[-1] - 1
-    assert intact.tolist() == nb.tolist()
-
-
 def test_flush_free_recovery_rebuilds_only_damaged_requests(oracle_lib):
     shape = W.TINY_BF16
     wl = W.small_workload(shape, [40, 17, 300, 129, 64, 0, 255], seed=511, other_live_frac=0.25)
