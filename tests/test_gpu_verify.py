@@ -113,8 +113,9 @@ def test_digests_and_verify_match_oracle(oracle_lib, case):
     arena.release()
 
 
-# entry and request counts on both sides of the inline lists' 256 and of one
-# workgroup per entry (2048); B = 1 makes every position an entry
+# entry and request counts on both sides of the 256 that the lists in the kernel
+# arguments hold, and up to 2049; B = 1 makes every position an entry, of 4 KB,
+# which one workgroup has to itself at any count (shared entries: the next test)
 @pytest.mark.parametrize("lens", [[256], [257], [1] * 256, [1] * 257, [2047], [2048, 1]])
 def test_digests_at_the_list_and_split_limits(oracle_lib, lens):
     shape = W.TINY_F32
@@ -133,6 +134,41 @@ def test_digests_at_the_list_and_split_limits(oracle_lib, lens):
     want = [min(int(n), len(bad) // 2 - int(a)) if a <= len(bad) // 2 < a + n else int(n)
             for a, n in zip(first, wl.lens)]
     assert intact.tolist() == want
+    arena.release()
+
+
+# entries whose planes are shared out over workgroups (256 KB and more, fewer than
+# 512 of them) on both sides of those lines and of the argument lists' 256; 300
+# entries take 7 workgroups each, which divide neither 10 planes nor 8.  Entries of
+# 240 KB are not shared.  Each request's last block is covered in part.
+@pytest.mark.parametrize("E", [1, 13, 256, 257, 300, 511, 512])
+@pytest.mark.parametrize("shape,B", [(W.LLAMA8B.with_layers(5), 16), (W.TINY_BF16, 64), (W.TINY_BF16, 60)],
+                         ids=["320KB", "256KB", "240KB"])
+def test_digests_of_shared_planes(oracle_lib, shape, B, E):
+    first = max(1, E // 3)
+    lens = [first * B - 7, (E - first) * B - 3] if E > 1 else [B - 7]
+    wl = W.small_workload(shape, lens, block_size=B, seed=561, other_live_frac=0.0)
+    assert kvr.num_entries(wl.lens, B) == E
+    say(f"digests of {E} entries of {2 * shape.num_layers} planes, {B} slots")
+    arena = Hn.DeviceArena(wl)
+    random_bits(arena, seed=89)
+    arena.bind()
+    o, _ = oracle_lib.verify(shape, arena.to_host(), B, wl.num_blocks, wl.lens, wl.block_tables)
+    assert np.array_equal(gpu_digests(arena, wl), o)
+    bad = o.copy()
+    bad[E - 1] += np.uint64(1)
+    want = ((wl.lens + B - 1) // B).tolist()
+    want[-1] -= 1
+    dg, intact = gpu_verify(arena, wl, bad)
+    assert np.array_equal(dg, o) and intact.tolist() == want
+    com = torch.from_numpy(bad.view(np.int64).copy()).cuda()
+    for own in (True, False):  # the digests in a poisoned buffer of the caller's, or in the scratch array
+        dg = torch.full((E,), -1, dtype=torch.int64, device="cuda")
+        intact = torch.full((len(lens),), -5, dtype=torch.int32, device="cuda")
+        kvr.kv_verify_noalloc(arena.handle, wl.lens, wl.block_tables, com.data_ptr(), intact.data_ptr(),
+                              dg.data_ptr() if own else 0, Hn.stream_ptr())
+        torch.cuda.synchronize()
+        assert intact.tolist() == want and (not own or np.array_equal(dg.cpu().numpy().view(np.uint64), o))
     arena.release()
 
 
