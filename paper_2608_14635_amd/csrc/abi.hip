@@ -324,7 +324,7 @@ kv_status check_request(const kv_model_desc* desc, int32_t B, int64_t NB, const 
 struct DecodeLayout {
   int32_t R = 0, npad = 0, splits = 0;
   int64_t max_position = 0;
-  size_t tok = 0, pos = 0, rowidx = 0, slot = 0, ctx = 0, tables = 0, meta_end = 0;
+  size_t tok = 0, pos = 0, rowidx = 0, slot = 0, first = 0, tables = 0, meta_end = 0;
   size_t rope = 0, x = 0, a = 0, q = 0, u = 0, hf = 0, part = 0, gpart = 0, amax = 0, logit = 0;
   size_t total = 0;
   int64_t gpart_elems = 0;
@@ -354,7 +354,7 @@ DecodeLayout make_decode_layout(const kv_model_desc& d, int32_t R, int64_t max_p
   L.pos = seg(4 * (size_t)R);
   L.rowidx = seg(4 * (size_t)R);
   L.slot = seg(8 * (size_t)R);
-  L.ctx = seg(4 * (size_t)R);
+  L.first = seg(4 * (size_t)R);
   L.tables = seg(4 * (size_t)R * (size_t)max_position);
   L.meta_end = off;
   L.rope = seg((size_t)8 * R * (d.head_dim / 2));
@@ -1134,9 +1134,12 @@ kv_status kv_decode_step(const kv_weights* w, const void* final_norm, const void
   int32_t* hpos = reinterpret_cast<int32_t*>(hb + L.pos);
   int32_t* hrow = reinterpret_cast<int32_t*>(hb + L.rowidx);
   int64_t* hslot = reinterpret_cast<int64_t*>(hb + L.slot);
-  int32_t* hctx = reinterpret_cast<int32_t*>(hb + L.ctx);
+  int32_t* hfirst = reinterpret_cast<int32_t*>(hb + L.first);
   int32_t* htab = reinterpret_cast<int32_t*>(hb + L.tables);
   const int32_t tab_ld = (int32_t)(max_pos / B + 1);  // staged table entries per request
+  // key ranges of the attention, numbered request by request
+  const int chunk = decode_attn_chunk(d.dtype, positions, R, d.num_kv_heads, max_pos + 1);
+  int items = 0;
   for (int32_t r = 0; r < R; ++r) {
     const int32_t p = positions[r];
     const int32_t* tab = tables + (int64_t)r * max_blocks;
@@ -1144,7 +1147,8 @@ kv_status kv_decode_step(const kv_weights* w, const void* final_norm, const void
     hpos[r] = p;
     hrow[r] = r;
     hslot[r] = (int64_t)tab[p / B] * B + p % B;
-    hctx[r] = p + 1;
+    hfirst[r] = items;
+    items += (int)(((int64_t)p + chunk) / chunk);
     for (int32_t b = 0; b < tab_ld; ++b) htab[(int64_t)r * tab_ld + b] = b <= p / B ? tab[b] : 0;
   }
   {
@@ -1168,7 +1172,7 @@ kv_status kv_decode_step(const kv_weights* w, const void* final_norm, const void
   const int32_t* d_pos = reinterpret_cast<const int32_t*>(ws + L.pos);
   const int32_t* d_row = reinterpret_cast<const int32_t*>(ws + L.rowidx);
   const int64_t* d_slot = reinterpret_cast<const int64_t*>(ws + L.slot);
-  const int32_t* d_ctx = reinterpret_cast<const int32_t*>(ws + L.ctx);
+  const int32_t* d_first = reinterpret_cast<const int32_t*>(ws + L.first);
   const int32_t* d_tab = reinterpret_cast<const int32_t*>(ws + L.tables);
   float2* rope = reinterpret_cast<float2*>(ws + L.rope);
   float* X = reinterpret_cast<float*>(ws + L.x);
@@ -1199,11 +1203,6 @@ kv_status kv_decode_step(const kv_weights* w, const void* final_norm, const void
     gemm(EPI_RESID, gp, s);
     launch_rmsnorm(dt, X, gain, A, R, H, eps, s);
   };
-
-  // key ranges of the attention
-  const int chunk = decode_attn_chunk(dt, positions, R, nkv, max_pos + 1);
-  int items = 0;
-  for (int32_t r = 0; r < R; ++r) items += (positions[r] + chunk) / chunk;
 
   // rope rows of the step's positions; the QKV epilogue indexes them by row
   launch_rope_rows(rope, d_pos, R, hd, d.rope_theta, s);
@@ -1252,7 +1251,8 @@ kv_status kv_decode_step(const kv_weights* w, const void* final_norm, const void
     ap.tables = d_tab;
     ap.max_blocks = tab_ld;
     ap.block_size = B;
-    ap.ctx = d_ctx;
+    ap.pos = d_pos;
+    ap.first = d_first;
     ap.nq = nq;
     ap.nkv = nkv;
     ap.d = hd;

@@ -20,6 +20,7 @@
 // and register-direct loads (decode_attn_mfma_kernel); the general one
 // serves fp32 models and other head sizes.
 #include <algorithm>
+#include <vector>
 
 #include "common.h"
 #include "launch.h"
@@ -57,30 +58,22 @@ __device__ __forceinline__ void load_vals8(const bf16_t* p, float* v) {
   v[6] = __uint_as_float(u.w << 16); v[7] = __uint_as_float(u.w & 0xffff0000u);
 }
 
-// Work item j of a step: key range `split` of request r.  Requests have
-// ceil(ctx / chunk) ranges each, numbered request by request; every wave finds
-// its own with a scan over the requests' counts, 64 at a time.
+// Work item j of a step: key range `split` of request r, the last request whose
+// first range is not past j.  Every wave looks it up itself, 64 requests a
+// probe: one load up to 64 requests, two up to 4096.  (A scan over the requests'
+// range counts, 64 at a time, cost a wave 8 us at 1024 requests.)
 __device__ __forceinline__ void find_range(const DecodeAttnParams& p, int j, int& r, int& split) {
   const int lane = threadIdx.x & 63;
-  int base = 0;
-  r = split = 0;
-  for (int r0 = 0; r0 < p.R; r0 += 64) {
-    const int n = r0 + lane < p.R ? (p.ctx[r0 + lane] + p.chunk - 1) / p.chunk : 0;
-    int incl = n;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int v = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += v;
-    }
-    const uint64_t past = __ballot(base + incl > j);
-    if (past != 0) {
-      const int f = __builtin_ctzll(past);
-      r = __builtin_amdgcn_readfirstlane(r0 + f);
-      split = __builtin_amdgcn_readfirstlane(j - base - __shfl(incl - n, f, 64));
-      return;
-    }
-    base += __shfl(incl, 63, 64);
+  r = 0;
+  for (int n = p.R; n > 1;) {
+    const int step = (n + 63) / 64;
+    const bool past = lane * step >= n || p.first[r + lane * step] > j;
+    const int k = __builtin_popcountll(__ballot(!past)) - 1;  // lane 0's is never past
+    r += k * step;
+    n = min(step, n - k * step);
   }
+  r = __builtin_amdgcn_readfirstlane(r);
+  split = j - p.first[r];
 }
 
 template <typename T>
@@ -98,7 +91,7 @@ __global__ __launch_bounds__(DNT) void decode_attn_kernel(DecodeAttnParams p) {
   find_range(p, blockIdx.x / p.nkv, r, split);
   const int g = p.nq / p.nkv, d = p.d;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int ctx = p.ctx[r];
+  const int ctx = p.pos[r] + 1;
   const int k0 = split * p.chunk, k1 = min(ctx, k0 + p.chunk);
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)d);
   const int64_t row_elems = (int64_t)p.nkv * d;  // one token slot of a plane
@@ -265,7 +258,7 @@ __global__ __launch_bounds__(256) void decode_attn_mfma_kernel(DecodeAttnParams 
   find_range(p, blockIdx.x / ngrp, r, split);
   const int g = p.nq / p.nkv;
   const int c = lane & 15, q = lane >> 4;
-  const int ctx = p.ctx[r];
+  const int ctx = p.pos[r] + 1;
   const int k0 = split * p.chunk, k1 = min(ctx, k0 + p.chunk);
   const float scale_log2 = 1.4426950408889634f / sqrtf(128.0f);
   const int64_t row_bytes = (int64_t)p.nkv * 128 * 2;
@@ -406,7 +399,7 @@ template <typename T>
 __global__ __launch_bounds__(DMAXD) void decode_combine_kernel(DecodeAttnParams p) {
   __shared__ float s_w[DMAXS], s_red[DMAXD];
   const int r = blockIdx.x / p.nq, h = blockIdx.x % p.nq;
-  const int e = threadIdx.x, d = p.d, S = (p.ctx[r] + p.chunk - 1) / p.chunk, stride = d + 2;
+  const int e = threadIdx.x, d = p.d, S = (p.pos[r] + p.chunk) / p.chunk, stride = d + 2;
   const float* base = p.part + ((int64_t)r * p.nq + h) * p.splits * stride;
   // M: maximum of the splits' m (order-free)
   float mloc = -INFINITY;
@@ -602,11 +595,20 @@ int decode_attn_chunk(int dtype, const int32_t* positions, int num_requests, int
   const int64_t most = decode_attn_max_splits(nkv, max_ctx);
   int64_t chunk = std::max<int64_t>({total * per / target, (max_ctx + most - 1) / most, 64});
   chunk = (chunk + 15) / 16 * 16;
-  for (;; chunk += std::max<int64_t>(16, chunk / 64 / 16 * 16)) {
+  // the first length, in steps of a 64th, that makes few enough ranges
+  std::vector<int64_t> steps{chunk};
+  while (steps.back() < max_ctx) steps.push_back(steps.back() + std::max<int64_t>(16, steps.back() / 64 / 16 * 16));
+  auto fits = [&](int64_t c) {
     int64_t items = 0;
-    for (int r = 0; r < num_requests; ++r) items += (positions[r] + chunk) / chunk;
-    if (items * per <= target || chunk >= max_ctx) return (int)chunk;
+    for (int r = 0; r < num_requests; ++r) items += (uint32_t)positions[r] / (uint32_t)c + 1;
+    return items * per <= target;
+  };
+  size_t lo = 0, hi = steps.size() - 1;
+  while (lo < hi) {
+    const size_t mid = (lo + hi) / 2;
+    if (fits(steps[mid])) hi = mid; else lo = mid + 1;
   }
+  return (int)steps[lo];
 }
 
 void launch_decode_attention(int dtype, const DecodeAttnParams& p, int items, hipStream_t s) {

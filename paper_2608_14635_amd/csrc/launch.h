@@ -169,10 +169,11 @@ struct DecodeAttnParams {
   const void* plane_v;    // this layer's V plane
   const int32_t* tables;  // [R][max_blocks] block tables
   int max_blocks, block_size;
-  const int32_t* ctx;     // [R] keys to attend (position + 1)
+  const int32_t* pos;     // [R] positions: request r attends pos[r] + 1 keys
+  const int32_t* first;   // [R] number of request r's first key range
   int R;
   int nq, nkv, d;
-  int chunk;              // keys per range, a multiple of 16: request r has ceil(ctx[r] / chunk) ranges
+  int chunk;              // keys per range, a multiple of 16: request r has ceil((pos[r] + 1) / chunk) ranges
   int splits;             // ranges of the longest request
   float* part;            // [R][nq][splits][d + 2] partials (o, m, l)
   void* out;              // [R][nq*d] attention output

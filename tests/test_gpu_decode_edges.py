@@ -34,11 +34,20 @@ CASES = {
 }
 
 
+# more requests than two probes of the range lookup tell apart
+def test_decode_of_4100_requests(oracle_lib):
+    shape = dataclasses.replace(T2, num_layers=1, hidden=256, ffn_dim=256, vocab=128)
+    check_step(oracle_lib, "4100 requests", shape, [1 + (i * i) % 11 for i in range(4100)], 0)
+
+
 @pytest.mark.parametrize("name", list(CASES))
 def test_decode_edges(oracle_lib, name):
-    shape, prefix, shift = CASES[name]
+    check_step(oracle_lib, name, *CASES[name])
+
+
+def check_step(oracle_lib, name, shape, prefix, shift, block_size=16):
     tol = PU.TOL[shape.dtype]
-    wl = TD.resume_workload(shape, prefix, steps=2, seed=801)
+    wl = TD.resume_workload(shape, prefix, steps=2, seed=801, block_size=block_size)
     R = len(prefix)
     TD.say(f"{name}: {R} requests")
     host_w, head = W.host_weights(shape, seed=802), W.host_head_weights(shape, seed=803)
