@@ -1138,7 +1138,7 @@ kv_status kv_decode_step(const kv_weights* w, const void* final_norm, const void
   int32_t* htab = reinterpret_cast<int32_t*>(hb + L.tables);
   const int32_t tab_ld = (int32_t)(max_pos / B + 1);  // staged table entries per request
   // key ranges of the attention, numbered request by request
-  const int chunk = decode_attn_chunk(d.dtype, positions, R, d.num_kv_heads, max_pos + 1);
+  const int chunk = decode_attn_chunk(d.dtype, B, positions, R, d.num_q_heads, d.num_kv_heads, d.head_dim, max_pos + 1);
   int items = 0;
   for (int32_t r = 0; r < R; ++r) {
     const int32_t p = positions[r];

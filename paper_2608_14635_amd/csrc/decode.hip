@@ -573,27 +573,53 @@ void launch_rope_rows(float2* table, const int32_t* positions, int rows, int d, 
                      positions, rows, half, theta, d);
 }
 
+// The matrix-core kernel takes bf16 heads of 128 in blocks of whole 16-key tiles,
+// four kv heads a workgroup; the general one takes the rest, one kv head each.
+static bool on_mfma(int dtype, int block_size, int g, int d) {
+  return dtype == 1 && d == 128 && block_size % DT == 0 && g <= 16;
+}
+
 int decode_attn_max_splits(int nkv, int64_t max_ctx) {
   const int64_t want = std::max<int64_t>((2048 + nkv - 1) / nkv, (max_ctx + 2047) / 2048);
   return (int)std::max<int64_t>(1, std::min<int64_t>(want, std::min<int64_t>(DMAXS, (max_ctx + 63) / 64)));
 }
 
-// The shortest ranges that give at most two workgroups to each of the 256 CUs,
-// so that they all start together and end together: HBM serves 16 requests of
-// equal lengths, two workgroups a CU, at 6.0 TB/s; of 2K to 16K positions in 16
-// ranges each, where the longest request's waves run on alone, at 5.3; in equal
-// ranges of 1.5 / 1.9 / 2.05 / 3 / 4 workgroups a CU a step (4 layers of the 8B
-// shape) took 1302 / 1270 / 1407 / 1366 / 1390 us, with 16 ranges each 1318.  Large batches get half as many again as they have
-// (request, head group) pairs.  At least 64 keys, and no more ranges than the
-// partials hold.
-int decode_attn_chunk(int dtype, const int32_t* positions, int num_requests, int nkv, int64_t max_ctx) {
-  const int64_t per = dtype == 1 ? (nkv + 3) / 4 : nkv;  // workgroups per range
+// The shortest ranges that make at most `target` workgroups, equal for all
+// requests.  Attention and combine of one layer, us, contexts of 1/8 to 2 times
+// the given mean:
+// Matrix-core kernel: two workgroups to each of the 256 CUs, so that they all
+// start together and end together: HBM serves 16 requests of equal lengths, two
+// workgroups a CU, at 6.0 TB/s; of 2K to 16K positions in 16 ranges each, where
+// the longest request's waves run on alone, at 5.3; in equal ranges of 1.5 / 1.9
+// / 2.05 / 3 / 4 workgroups a CU a step (4 layers of the 8B shape) took 1302 /
+// 1270 / 1407 / 1366 / 1390 us, with 16 ranges each 1318.  More than 8 q heads a
+// kv head fill a CU's registers with one workgroup: 256 of them until requests
+// alone make more (4 kv heads, 16 requests of 8000: 88 against 101 with 512).
+// General kernel: bf16 has room for three a CU (LDS); with 256 pairs of request
+// and kv head or more, ranges near whole requests balance badly (8 kv heads, 16
+// requests of 8000: 768 / 1024 / 2048 workgroups 163 / 207 / 174; 128 of 1000:
+// 1536 / 2048 214 / 205).  fp32 has room for one, and 512 in two rounds beat 256
+// on ragged batches (16 of 8000: 482 against 563); from 384 pairs on, 64 of 2000:
+// 768 / 2048 649 / 544.
+// Beyond a target's pairs, half as many workgroups again as pairs; where there
+// are 2048 pairs, no range below 512 keys (2048 requests of 100, 8 kv heads in
+// fp32: 1251 with ranges of about 128, 1144 whole).  At least 64 keys, and no
+// more ranges than the partials hold.
+int decode_attn_chunk(int dtype, int block_size, const int32_t* positions, int num_requests, int nq, int nkv, int d,
+                      int64_t max_ctx) {
+  const int g = nq / nkv;
+  const bool mfma = on_mfma(dtype, block_size, g, d);
+  const int64_t per = mfma ? (nkv + 3) / 4 : nkv;  // workgroups per range
   const int64_t pairs = num_requests * per;
-  const int64_t target = std::max<int64_t>(512, (pairs + pairs / 2 + 255) / 256 * 256);
+  int64_t target = 512;
+  if (mfma && g > 8 && pairs <= 64) target = 256;
+  if (!mfma && dtype == 1) target = pairs <= 256 ? 768 : 2048;
+  if (!mfma && dtype == 0 && pairs >= 384) target = 2048;
+  target = std::max<int64_t>(target, (pairs + pairs / 2 + 255) / 256 * 256);
   int64_t total = 0;
   for (int r = 0; r < num_requests; ++r) total += positions[r] + 1;
   const int64_t most = decode_attn_max_splits(nkv, max_ctx);
-  int64_t chunk = std::max<int64_t>({total * per / target, (max_ctx + most - 1) / most, 64});
+  int64_t chunk = std::max<int64_t>({total * per / target, (max_ctx + most - 1) / most, pairs >= 2048 ? 512 : 64});
   chunk = (chunk + 15) / 16 * 16;
   // the first length, in steps of a 64th, that makes few enough ranges
   std::vector<int64_t> steps{chunk};
@@ -617,7 +643,7 @@ void launch_decode_attention(int dtype, const DecodeAttnParams& p, int items, hi
   const dim3 grid((unsigned)((int64_t)items * p.nkv));
   const dim3 cgrid((unsigned)((int64_t)num_requests * p.nq));
   const int g = p.nq / p.nkv;
-  if (dtype == 1 && p.d == 128 && p.block_size % DT == 0 && g <= 16) {
+  if (on_mfma(dtype, p.block_size, g, p.d)) {
     const dim3 mgrid((unsigned)((int64_t)items * ((p.nkv + 3) / 4)));
     if (g <= 4)
       hipLaunchKernelGGL(decode_attn_mfma_kernel<4>, mgrid, dim3(256), 0, s, p);

@@ -183,7 +183,8 @@ void launch_rope_rows(float2* table, const int32_t* positions, int rows, int d, 
 // Most ranges a request may have (the workspace's partials are sized for it)
 // and the range length of a step: equal ranges for all requests.
 int decode_attn_max_splits(int nkv, int64_t max_ctx);
-int decode_attn_chunk(int dtype, const int32_t* positions, int num_requests, int nkv, int64_t max_ctx);
+int decode_attn_chunk(int dtype, int block_size, const int32_t* positions, int num_requests, int nq, int nkv, int d,
+                      int64_t max_ctx);
 // items: ranges of all requests
 void launch_decode_attention(int dtype, const DecodeAttnParams& p, int items, hipStream_t s);
 constexpr int ARGMAX_CHUNKS = 256;  // vocab chunks of the first argmax pass

@@ -34,6 +34,25 @@ CASES = {
 }
 
 
+# the general attention kernel in bf16 (blocks that hold no whole 16-key tiles) over
+# several ranges a request; it and the matrix-core kernel where the number of
+# requests changes the length of the ranges
+KERNELS = {
+    "b8_ragged": (T2, [1, 63, 64, 65, 700, 1500, 129], 8),
+    "b24_ragged": (T2, [1, 63, 64, 65, 700, 1500, 129], 24),
+    "b8_130req": (T2.with_layers(1), [1 + (37 * i) % 301 for i in range(130)], 8),
+    "f32_95req": (W.TINY_F32.with_layers(1), [1 + (37 * i) % 301 for i in range(95)], 16),
+    "f32_96req": (W.TINY_F32.with_layers(1), [1 + (37 * i) % 301 for i in range(96)], 16),
+    "g16_65req": (dataclasses.replace(T2.with_layers(1), num_q_heads=32), [1 + (37 * i) % 301 for i in range(65)], 16),
+}
+
+
+@pytest.mark.parametrize("name", list(KERNELS))
+def test_decode_kernels_and_ranges(oracle_lib, name):
+    shape, prefix, block_size = KERNELS[name]
+    check_step(oracle_lib, name, shape, prefix, 0, block_size)
+
+
 # more requests than two probes of the range lookup tell apart
 def test_decode_of_4100_requests(oracle_lib):
     shape = dataclasses.replace(T2, num_layers=1, hidden=256, ffn_dim=256, vocab=128)
