@@ -510,7 +510,7 @@ __global__ __launch_bounds__(256) void argmax_partial_kernel(const float* logits
 }
 
 // Pass 1 over row-major logits [R][ld]: workgroup (c, y) scans vocabulary chunk
-// c of requests 4y .. 4y+3, one per wave, its lanes consecutive entries (eight
+// c of requests 4y .. 4y+3 (and on, where a grid has no room for all), one per wave, its lanes consecutive entries (eight
 // per lane in flight), and merges its lanes with shuffles.  (With one workgroup
 // per chunk, its waves walking the requests, 100 requests over 152064 entries
 // took 71 us.)
@@ -519,8 +519,7 @@ __global__ __launch_bounds__(256) void argmax_rows_partial_kernel(const float* l
   const int c = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int per = (vocab + ARGMAX_CHUNKS - 1) / ARGMAX_CHUNKS;
   const int v0 = c * per, v1 = min(vocab, v0 + per);
-  const int r = blockIdx.y * 4 + w;
-  if (r < R) {
+  for (int r = blockIdx.y * 4 + w; r < R; r += gridDim.y * 4) {
     const float* row = logits + (int64_t)r * ld;
     float best = -INFINITY;
     int bi = -1;
@@ -673,8 +672,8 @@ void launch_argmax(const float* logits_t, int64_t ld, int vocab, int num_request
 void launch_argmax_rows(const float* logits, int64_t ld, int vocab, int num_requests,
                         float2* partial, int32_t* next_tokens, hipStream_t s) {
   if (num_requests <= 0) return;
-  hipLaunchKernelGGL(argmax_rows_partial_kernel, dim3(ARGMAX_CHUNKS, (num_requests + 3) / 4), dim3(256), 0, s,
-                     logits, ld, vocab, num_requests, partial);
+  const dim3 grid(ARGMAX_CHUNKS, std::min((num_requests + 3) / 4, 65535));
+  hipLaunchKernelGGL(argmax_rows_partial_kernel, grid, dim3(256), 0, s, logits, ld, vocab, num_requests, partial);
   hipLaunchKernelGGL(argmax_final_kernel, dim3(num_requests), dim3(64), 0, s, partial,
                      num_requests, next_tokens);
 }

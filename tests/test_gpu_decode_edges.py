@@ -135,3 +135,29 @@ def test_decode_v_that_is_not_finite_stays_in_its_dim(oracle_lib, R):
     assert (g[0, 1, :, 3] == np.inf).all() and np.isnan(g[0, 1, :, 228]).all()
     ok = np.isfinite(o)
     assert TD.rel(g[ok], o[ok]) <= PU.TOL[W.BF16]
+
+
+def test_decode_of_more_requests_than_a_grid_is_wide(oracle_lib):
+    """262,148 requests at position 0, 128 tokens over and over: each gets the token
+    the first with its own gets, and those are the oracle's."""
+    R, n = 262148, 128
+    shape = dataclasses.replace(T2, num_layers=1, hidden=256, num_q_heads=2, num_kv_heads=2, ffn_dim=128, vocab=n)
+    TD.say(f"{R} requests")
+    host_w, head = W.host_weights(shape, seed=821), W.host_head_weights(shape, seed=822)
+    model, hd = Hn.device_model_from_host(shape, host_w), Hn.device_head_from_host(shape, head)
+    bits = torch.zeros(1, 2, R, 1, 2, 128, dtype=torch.int16, device="cuda")
+    handle = kvr.kv_arena_bind(bits.data_ptr(), bits.numel() * 2, shape, 1, R)
+    tok, pos = (np.arange(R) % n).astype(np.int32), np.zeros(R, np.int32)
+    nbytes = kvr.kv_decode_workspace_bytes(shape, R, 1)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    nxt = torch.full((R,), -1, dtype=torch.int32, device="cuda")
+    kvr.kv_decode_step(model.weights, hd["final_norm"].data_ptr(), hd["lm_head"].data_ptr(), tok, pos,
+                       np.arange(R, dtype=np.int32)[:, None], handle, ws.data_ptr(), nbytes, nxt.data_ptr(), 0,
+                       Hn.stream_ptr())
+    torch.cuda.synchronize()
+    kvr.kv_arena_release(handle)
+    got = nxt.cpu().numpy()
+    image = np.zeros(2 * n * 2 * 128, np.uint16)
+    fh = oracle_lib.decode_step(shape, host_w, tok[:n], pos[:n], np.arange(n, dtype=np.int32)[:, None], image, 1, n)
+    TD.assert_valid_argmax(got[:n], oracle_lib.logits(shape, head, fh), PU.TOL[shape.dtype])
+    assert np.array_equal(got, np.resize(got[:n], R))
