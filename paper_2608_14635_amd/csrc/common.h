@@ -10,6 +10,10 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// the same in memory that is aligned for 8-byte or for 4-byte elements only: the
+// compiler may assume no more, and the hardware takes 16 bytes on any 4-byte boundary
+typedef f32x4 f32x4_a8 __attribute__((aligned(8)));
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
 
 // bf16 values are stored as raw 16-bit patterns
 typedef uint16_t bf16_t;

@@ -381,8 +381,9 @@ __global__ __launch_bounds__(256) void decode_attn_mfma_kernel(DecodeAttnParams 
   for (int h = 0; h < GM; ++h) {
     if (h < g) {
       float* dst = p.part + (((int64_t)r * p.nq + kvh * g + h) * S + split) * stride + 8 * c;
-      *reinterpret_cast<float4*>(dst) = make_float4(o[h][0], o[h][1], o[h][2], o[h][3]);
-      *reinterpret_cast<float4*>(dst + 4) = make_float4(o[h][4], o[h][5], o[h][6], o[h][7]);
+      // rows of 130 floats: 8-byte aligned
+      reinterpret_cast<f32x4_a8*>(dst)[0] = f32x4{o[h][0], o[h][1], o[h][2], o[h][3]};
+      reinterpret_cast<f32x4_a8*>(dst)[1] = f32x4{o[h][4], o[h][5], o[h][6], o[h][7]};
     }
   }
   if (c < g) {
