@@ -235,7 +235,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(GemmParams p, i
     for (int i = 0; i < RI; ++i)
       if (row(i) < p.M)
 #pragma unroll
-        for (int j = 0; j < CJ; ++j) *reinterpret_cast<f32x4*>(out + row(i) * ld + nb + col(j)) = acc[i][j];
+        for (int j = 0; j < CJ; ++j)  // (a caller's logits may start on any float)
+          *reinterpret_cast<f32x4_a4*>(out + row(i) * ld + nb + col(j)) = acc[i][j];
   }
 }
 

@@ -104,8 +104,8 @@ int64_t gemm_bf16_splitk_part_elems(int M, int N, int K);
 void launch_gemm_bf16_resid_norm(const GemmParams& p, float* part, int64_t part_cap, const void* gain,
                                  void* a_out, float eps, hipStream_t s);
 // fp32 C[M][N] = A . B^T written to out (row stride ldo), no epilogue; plain B
-// rows.  Returns false, launching nothing, unless out is 16-byte aligned,
-// ldo % 4 == 0 and N is a multiple of 16 (of 128 for more than 64 rows).
+// rows.  Returns false, launching nothing, unless N is a multiple of 16 (of 128
+// for more than 64 rows).
 bool launch_gemm_bf16_rows(const GemmParams& p, float* out, int64_t ldo, hipStream_t s);
 
 // Attention.  qblk: per q-block int4 {q_start, q_len, req_start, 0} in

@@ -2,8 +2,7 @@
 requests than one wave of the range scan (64) and than the few-row products (64),
 ragged contexts on both sides of a key range's length, vocabularies that end on
 each column block of the row-major LM head, per-head norms with few rows, and a
-logits buffer that is only 4-byte aligned (the transposed LM head).  Tolerances
-as in test_gpu_decode."""
+logits buffer that is only 4-byte aligned.  Tolerances as in test_gpu_decode."""
 import dataclasses
 
 import numpy as np
@@ -135,6 +134,25 @@ def test_decode_v_that_is_not_finite_stays_in_its_dim(oracle_lib, R):
     assert (g[0, 1, :, 3] == np.inf).all() and np.isnan(g[0, 1, :, 228]).all()
     ok = np.isfinite(o)
     assert TD.rel(g[ok], o[ok]) <= PU.TOL[W.BF16]
+
+
+@pytest.mark.parametrize("R", [4, 66])
+def test_logits_do_not_depend_on_their_buffers_alignment(R):
+    shape = dataclasses.replace(T2, num_layers=1, vocab=1024)
+    wl = TD.resume_workload(shape, [1] * R, steps=2, seed=841)
+    TD.say(f"{R} requests, logits 0 to 3 floats past a 16-byte boundary")
+    model = Hn.device_model_random(shape, seed=842)
+    GD = TD.GpuDecoder(wl, model, Hn.device_head_random(shape, seed=843), 1)
+    arena = Hn.DeviceArena(wl)
+    arena.bind()
+    raw = torch.zeros(R * shape.vocab + 4, dtype=torch.float32, device="cuda")
+    got = []
+    for shift in range(4):
+        GD.logits = raw[shift:shift + R * shape.vocab].view(R, shape.vocab)
+        got.append(GD.step(arena, np.arange(R, dtype=np.int32), np.zeros(R, np.int32)))
+    arena.release()
+    for tok, logits in got[1:]:
+        assert np.array_equal(tok, got[0][0]) and np.array_equal(logits.view(np.uint32), got[0][1].view(np.uint32))
 
 
 def test_decode_of_more_requests_than_a_grid_is_wide(oracle_lib):
