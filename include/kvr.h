@@ -24,7 +24,8 @@
  *     kv_last_error() returns a message for the calling thread.
  *   - "device" pointers are HIP device allocations on the arena's device;
  *     "host" pointers are ordinary CPU memory.  The library never frees or
- *     takes ownership of caller memory.
+ *     takes ownership of caller memory.  Device arrays start on any boundary of
+ *     their elements (bf16 ones of 4 bytes), workspaces on any of 16 bytes.
  *   - Streams are hipStream_t values passed as void* (NULL = default stream).
  *   - All argument errors are detected on the host before any device work is
  *     enqueued, so a rejected call leaves the arena untouched.

@@ -365,8 +365,8 @@ __global__ __launch_bounds__(256, HD <= 32 ? 4 : HD == 64 ? 3 : 1) void attn_f32
       ka[i] = va[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};  // keys past the end: inert
       if (j < nkeys) {
         const int64_t off = p.kslot[key_base + j] * row_elems + u * 4;
-        ka[i] = *reinterpret_cast<const f32x4*>(Kp + off);
-        va[i] = *reinterpret_cast<const f32x4*>(Vp + off);
+        ka[i] = *reinterpret_cast<const f32x4_a4*>(Kp + off);
+        va[i] = *reinterpret_cast<const f32x4_a4*>(Vp + off);
       }
     }
   };

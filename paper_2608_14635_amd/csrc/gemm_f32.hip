@@ -17,6 +17,7 @@
 // fp32 matrix cores (64 x 64 tiles).
 // Every output is produced by one workgroup in one K order: results do not
 // depend on the other rows of a call.
+// Weights, biases, gains and the arena come from the caller on any 4-byte boundary.
 #include "common.h"
 #include "launch.h"
 
@@ -96,7 +97,7 @@ __device__ __forceinline__ void qkv_f32(f32x4 (&acc)[RI][CJ], int M, int n0, con
   if (bias != nullptr) {
 #pragma unroll
     for (int j = 0; j < CJ; ++j) {
-      const f32x4 b = *reinterpret_cast<const f32x4*>(bias + hd[j] * d + dim[j]);
+      const f32x4 b = *reinterpret_cast<const f32x4_a4*>(bias + hd[j] * d + dim[j]);
 #pragma unroll
       for (int i = 0; i < RI; ++i)
 #pragma unroll
@@ -133,7 +134,7 @@ __device__ __forceinline__ void qkv_f32(f32x4 (&acc)[RI][CJ], int M, int n0, con
 #pragma unroll
           for (int j = 0; j < CJ; ++j) {
             const float inv = 1.0f / sqrtf(ss[j] / (float)d + e.eps);
-            const f32x4 g = *reinterpret_cast<const f32x4*>(gain + dim[j]);
+            const f32x4 g = *reinterpret_cast<const f32x4_a4*>(gain + dim[j]);
 #pragma unroll
             for (int k = 0; k < 4; ++k) acc[i][j][k] = acc[i][j][k] * inv * g[k];
           }
@@ -177,7 +178,7 @@ __device__ __forceinline__ void qkv_f32(f32x4 (&acc)[RI][CJ], int M, int n0, con
       dst = reinterpret_cast<float*>(region == 1 ? e.arena_k : e.arena_v) + sl * kcols;
     }
 #pragma unroll
-    for (int j = 0; j < CJ; ++j) *reinterpret_cast<f32x4*>(dst + hd[j] * d + dim[j]) = acc[i][j];
+    for (int j = 0; j < CJ; ++j) *reinterpret_cast<f32x4_a4*>(dst + hd[j] * d + dim[j]) = acc[i][j];
   }
 }
 
@@ -300,12 +301,12 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_f32_kernel(GemmParams p, in
 #pragma unroll
       for (int i = 0; i < RI; ++i) {
         a[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if (k < p.K) a[i] = *reinterpret_cast<const f32x4*>(A + (int64_t)min(row(i) - m0, rows_a - 1) * p.lda + k);
+        if (k < p.K) a[i] = *reinterpret_cast<const f32x4_a4*>(A + (int64_t)min(row(i) - m0, rows_a - 1) * p.lda + k);
       }
 #pragma unroll
       for (int j = 0; j < CJ; ++j) {
         b[j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if (k < p.K) b[j] = *reinterpret_cast<const f32x4*>(b_row<EPI>(p, n0, wn * WC + j * 16 + fr) + k);
+        if (k < p.K) b[j] = *reinterpret_cast<const f32x4_a4*>(b_row<EPI>(p, n0, wn * WC + j * 16 + fr) + k);
       }
       multiply(a, b);
     }
