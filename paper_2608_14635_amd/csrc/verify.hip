@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "launch.h"
 
@@ -35,21 +36,35 @@ __device__ __forceinline__ uint64_t sq_words(u32x4 v, uint32_t k) {
   return (uint64_t)x0 * x0 + (uint64_t)x1 * x1 + (uint64_t)x2 * x2 + (uint64_t)x3 * x3;
 }
 
-// INL: the entries come with the arguments
-template <bool INL>
-__global__ __launch_bounds__(DG_THREADS) void block_digest_kernel(DigestParams p, InlineEntries in) {
+// The kernels' lists come with the arguments (In = InlineEntries, InlineOffsets) or
+// from memory (In = NoList: two kilobytes of unused arguments cost a launch 1 us).
+struct NoList {};
+template <typename In>
+constexpr bool INL = !std::is_same<In, NoList>::value;
+
+template <typename In>
+__global__ __launch_bounds__(DG_THREADS) void block_digest_kernel(DigestParams p, In in) {
   __shared__ uint64_t red[DG_THREADS];
-  const int64_t e = blockIdx.x / p.parts;
-  const int part = (int)(blockIdx.x % p.parts);
-  const int2 ent = INL ? in.entries[e] : p.entries[e];
+  int64_t e = blockIdx.x;
+  int pl = 0, pl1 = p.planes;
+  if (p.parts > 1) {
+    const int part = (int)(blockIdx.x % p.parts);
+    e = blockIdx.x / p.parts;
+    pl = part * p.planes / p.parts;
+    pl1 = (part + 1) * p.planes / p.parts;
+  }
+  int2 ent;
+  if constexpr (INL<In>)
+    ent = in.entries[e];
+  else
+    ent = p.entries[e];
   const int64_t nbytes = (int64_t)ent.y * p.row_bytes;
   const int cpp = (int)(nbytes >> 4);            // 16-byte chunks per plane
   const uint32_t wpp = (uint32_t)(nbytes >> 2);  // words per plane (mod 2^32)
   const char* base = p.arena + (int64_t)ent.x * p.block_bytes;
   const int t = threadIdx.x;
   uint64_t acc = 0;
-  const int pl1 = (part + 1) * p.planes / p.parts;
-  for (int pl = part * p.planes / p.parts; pl < pl1; ++pl) {
+  for (; pl < pl1; ++pl) {
     const u32x4* src = reinterpret_cast<const u32x4*>(base + (int64_t)pl * p.plane_bytes);
     const uint32_t ibase = (uint32_t)pl * wpp;
     int c0 = t;
@@ -86,16 +101,15 @@ __global__ __launch_bounds__(DG_THREADS) void clear_digests_kernel(uint64_t* dig
   if (i < n) digests[i] = 0;
 }
 
-template <bool INL>
-__global__ __launch_bounds__(DG_THREADS) void leading_intact_kernel(const int32_t* offsets,
-                                                                    InlineOffsets in,
+template <typename In>
+__global__ __launch_bounds__(DG_THREADS) void leading_intact_kernel(const int32_t* offsets, In in,
                                                                     const uint64_t* digests,
                                                                     const uint64_t* committed,
                                                                     int32_t* intact) {
   __shared__ int32_t red[DG_THREADS];
   const int r = blockIdx.x;
-  const int32_t off = INL ? in.offsets[r] : offsets[r];
-  const int32_t nb = (INL ? in.offsets[r + 1] : offsets[r + 1]) - off;
+  if constexpr (INL<In>) offsets = in.offsets;
+  const int32_t off = offsets[r], nb = offsets[r + 1] - off;
   const int t = threadIdx.x;
   int32_t first = nb;
   // the first mismatch among entries t, t+256, ...; the minimum over lanes is the first overall
@@ -178,21 +192,20 @@ void launch_block_digest(const DigestParams& p_in, const InlineEntries* in, hipS
                            s>>>(p.digests, p.num_entries);
   const dim3 grid((unsigned)(p.num_entries * p.parts));
   if (in)
-    block_digest_kernel<true><<<grid, dim3(DG_THREADS), 0, s>>>(p, *in);
+    block_digest_kernel<<<grid, dim3(DG_THREADS), 0, s>>>(p, *in);
   else
-    block_digest_kernel<false><<<grid, dim3(DG_THREADS), 0, s>>>(p, InlineEntries{});
+    block_digest_kernel<<<grid, dim3(DG_THREADS), 0, s>>>(p, NoList{});
 }
 
 void launch_leading_intact(const int32_t* offsets, const InlineOffsets* in, int32_t num_requests,
                            const uint64_t* digests, const uint64_t* committed, int32_t* intact,
                            hipStream_t s) {
   if (num_requests <= 0) return;
+  const dim3 grid((unsigned)num_requests);
   if (in)
-    leading_intact_kernel<true><<<dim3((unsigned)num_requests), dim3(DG_THREADS), 0, s>>>(offsets, *in, digests,
-                                                                                          committed, intact);
+    leading_intact_kernel<<<grid, dim3(DG_THREADS), 0, s>>>(offsets, *in, digests, committed, intact);
   else
-    leading_intact_kernel<false><<<dim3((unsigned)num_requests), dim3(DG_THREADS), 0, s>>>(
-        offsets, InlineOffsets{}, digests, committed, intact);
+    leading_intact_kernel<<<grid, dim3(DG_THREADS), 0, s>>>(offsets, NoList{}, digests, committed, intact);
 }
 
 }  // namespace kvr
