@@ -31,13 +31,13 @@ PEAK_FP32_TFLOPS = 157.3
 PEAK_HBM_GBS = 8000.0
 
 # kernel class -> sources whose text fixes that kernel's code
-GEMM_SOURCES = ["gemm_wide.hip", "gemm_tile.hip", "gemm_epi.h", "common.h", "launch.h"]
+GEMM_SOURCES = ["gemm_wide.hip", "gemm_tile.hip", "gemm_epi.h", "dma.h", "common.h", "launch.h"]
 KERNEL_SOURCES = {
     "gemm_qkv": GEMM_SOURCES,
     "gemm_o": GEMM_SOURCES,
     "gemm_gateup": GEMM_SOURCES,
     "gemm_down": GEMM_SOURCES,
-    "attention": ["attention.hip", "common.h", "launch.h"],
+    "attention": ["attention.hip", "dma.h", "common.h", "launch.h"],
     "verify": ["verify.hip", "launch.h"],
 }
 

@@ -24,6 +24,7 @@
 //
 // fp32 path: the same on the fp32 matrix cores, straight from the arena rows.
 #include "common.h"
+#include "dma.h"
 #include "launch.h"
 
 namespace kvr {
@@ -40,8 +41,6 @@ constexpr int NSTAGE = 3;
 constexpr float RESCALE_SLACK = 8.0f;        // see the online softmax below
 static_assert(KB == VT_KEYS, "a key tile is one tile of the V^T copy");
 constexpr int READ_AHEAD = 4;                // LDS fragment reads in flight ahead of the MFMAs
-
-typedef __attribute__((address_space(3))) void lds_void;
 
 // LDS row r of a K tile holds key ksig(r): bits 2 and 3 swapped (an involution)
 __device__ __forceinline__ int ksig(int r) { return (r & ~12) | ((r & 4) << 1) | ((r & 8) >> 1); }
@@ -63,11 +62,6 @@ __device__ __forceinline__ float sum_with_other_half(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-
-#define KVR_WAIT_VMCNT(n) \
-  __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (((n) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
-
-constexpr int BUF_WORD3 = 0x00020000;  // gfx9 buffer descriptor: 32-bit data format
 
 // Issue this wave's share (2 K blocks + 2 V^T blocks of 1 KB) of key tile
 // starting at row kbase into ring stage `stage`.  Buffer loads with the LDS

@@ -19,6 +19,7 @@
 // depend on the other rows of a call.
 // Weights, biases, gains and the arena come from the caller on any 4-byte boundary.
 #include "common.h"
+#include "dma.h"
 #include "launch.h"
 
 namespace kvr {
@@ -26,23 +27,6 @@ namespace kvr {
 namespace {
 
 constexpr int BK = 32;  // floats: 128 bytes
-typedef __attribute__((address_space(3))) void lds_void;
-constexpr int BUF_WORD3 = 0x00020000;  // gfx9 buffer descriptor: 32-bit data format
-
-// s_waitcnt with only the vector-memory / only the LDS counter constrained
-#define KVR_WAIT_VMCNT(n) \
-  __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (((n) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
-#define KVR_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4))
-
-// LDS operand rows of 128 bytes: 16-byte unit u of row r (of 16) at slot
-// u ^ swz(r), conflict-free for the 16-row operand reads (gemm_wide.hip)
-__device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
-
-// One direct-to-LDS load: 16 bytes per lane from base + voff + soff to 1 KB at dst
-__device__ __forceinline__ void load_lds(const void* base, int bytes, char* dst, int voff, int soff) {
-  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, BUF_WORD3);
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)dst, 16, voff, soff, 0, 0);
-}
 
 // Weight row (within its head) of a column: 32-column groups of 16 dims and
 // their rotary partners, so that a lane holds both (head dim 32 and up; at 16

@@ -34,6 +34,7 @@
 // products added in index order: results are deterministic and do not depend
 // on the tile size or on the other rows of the call.
 #include "common.h"
+#include "dma.h"
 #include "gemm_epi.h"
 #include "launch.h"
 
@@ -45,23 +46,6 @@ constexpr int BM = 256, BN = 256, BK = 64, WAVES = 8, NT = 64 * WAVES;
 constexpr int SLOTS = 8;
 constexpr int HALF_BYTES = 128 * BK * 2;  // one half tile
 constexpr int LDS_BYTES = SLOTS * HALF_BYTES;
-
-typedef __attribute__((address_space(3))) void lds_void;
-constexpr int BUF_WORD3 = 0x00020000;  // gfx9 buffer descriptor: 32-bit data format
-
-// s_waitcnt with only the vector-memory / only the LDS counter constrained
-#define KVR_WAIT_VMCNT(n) \
-  __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (((n) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
-#define KVR_WAIT_LGKM0() __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4))
-
-// LDS layout of a half tile: 1 KB blocks of 8 rows of 128 bytes; row r (of 16)
-// holds its 16-byte k-unit u at slot u ^ swz(r).  A direct-to-LDS load writes
-// 64 lanes x 16 B contiguously, so one instruction fills one block with whole
-// 128-byte rows.  The LDS serves a b128 read 16 lanes at a time, lanes 0-3,
-// 12-15 and 20-27 in one pass: with rows 0-15 at unit u in lanes 0-15 and at
-// unit u+1 in lanes 16-31 this swizzle puts each pass on 64 distinct banks
-// (r ^ (r >> 3) took two passes for every one).
-__device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
 // Half tiles by kind, in stream order over two K tiles.
 enum Kind { A0 = 0, A1 = 1, B0 = 2, B1 = 3 };
@@ -132,11 +116,9 @@ __global__ __launch_bounds__(NT, 2) void gemm_wide_kernel(GemmParams p, int tile
   auto issue = [&](int kind, int kt, int slot) {
     char* dst = smem + slot * HALF_BYTES + wave * 1024;
     const Operand& o = kind < 2 ? oa : ob;
-    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(o.base), 0, o.bytes, BUF_WORD3);
+    const int kb = min(kt, KT - 1) * BK * 2;
 #pragma unroll
-    for (int q = 0; q < 2; ++q)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)(dst + q * 8192), 16, o.voff[kind & 1][q],
-                                               min(kt, KT - 1) * BK * 2, 0, 0);
+    for (int q = 0; q < 2; ++q) load_lds(o.base, o.bytes, dst + q * 8192, o.voff[kind & 1][q], kb);
   };
 #pragma unroll
   for (int n = 0; n < SLOTS; ++n) issue(KIND[n], n >> 2, n);
