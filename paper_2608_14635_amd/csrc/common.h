@@ -29,12 +29,10 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 template <typename T> struct Elem;
 template <> struct Elem<float> {
   static __device__ __forceinline__ float load(const float* p, int64_t i) { return p[i]; }
-  static __device__ __forceinline__ float round(float v) { return v; }
   static __device__ __forceinline__ void store(float* p, int64_t i, float v) { p[i] = v; }
 };
 template <> struct Elem<bf16_t> {
   static __device__ __forceinline__ float load(const bf16_t* p, int64_t i) { return bf2f(p[i]); }
-  static __device__ __forceinline__ float round(float v) { return bf2f(f2bf(v)); }
   static __device__ __forceinline__ void store(bf16_t* p, int64_t i, float v) { p[i] = f2bf(v); }
 };
 
@@ -52,17 +50,13 @@ __device__ __forceinline__ void store8(float* p, const float* v) {
   reinterpret_cast<float4*>(p)[1] = make_float4(v[4], v[5], v[6], v[7]);
 }
 
-// Load 8 consecutive values as fp32 (one 16-byte load for bf16, two for fp32).
+// Load 8 consecutive bf16 values as fp32 (one 16-byte load).
 __device__ __forceinline__ void ld8(const bf16_t* p, float* v) {
   const uint4 u = *reinterpret_cast<const uint4*>(p);
   v[0] = __uint_as_float(u.x << 16); v[1] = __uint_as_float(u.x & 0xffff0000u);
   v[2] = __uint_as_float(u.y << 16); v[3] = __uint_as_float(u.y & 0xffff0000u);
   v[4] = __uint_as_float(u.z << 16); v[5] = __uint_as_float(u.z & 0xffff0000u);
   v[6] = __uint_as_float(u.w << 16); v[7] = __uint_as_float(u.w & 0xffff0000u);
-}
-__device__ __forceinline__ void ld8(const float* p, float* v) {
-  const float4 a = reinterpret_cast<const float4*>(p)[0], b = reinterpret_cast<const float4*>(p)[1];
-  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
 }
 
 // silu(g) = g * sigmoid(g); the reciprocal is v_rcp_f32 (1 ulp), far below

@@ -51,8 +51,7 @@ __device__ __forceinline__ void sum_splits(const float* const (&src)[IPT], const
   }
 }
 
-// TW: the epilogue's tile width, BN or (QKV, head dim dividing 128) 128 for
-// twice the workgroups
+// TW: the epilogue's tile width, a head for QKV and BN for SWIGLU
 template <int EPI, int TW>
 __global__ __launch_bounds__(256) void splitk_epi_kernel(GemmParams p, int tiles_n) {
   __shared__ __attribute__((aligned(16))) float sC[SK_ROWS * LDC];
@@ -77,9 +76,9 @@ __global__ __launch_bounds__(256) void splitk_epi_kernel(GemmParams p, int tiles
   }
   __syncthreads();
   if (EPI == EPI_QKV) {
-    epi_qkv<bf16_t, TW, 256>(sC, LDC, SK_ROWS, m0, p.M, p.n_begin + tile_n * TW, p.epi);
+    epi_qkv<256>(sC, LDC, SK_ROWS, m0, p.M, p.n_begin + tile_n * TW, p.epi);
   } else {
-    epi_swiglu<bf16_t, BN, 256>(sC, LDC, SK_ROWS, m0, p.M, tile_n * (BN / 2), p.epi);
+    epi_swiglu<BN, 256>(sC, LDC, SK_ROWS, m0, p.M, tile_n * (BN / 2), p.epi);
   }
 }
 
@@ -241,9 +240,9 @@ __global__ __launch_bounds__(64 * SK_W) void gemm_rows_kernel(GemmParams p) {
 }
 
 // Residual sum and RMSNorm after a few-row product: workgroup m sums row m's
-// split-K partials in split order into the residual row X (the values
-// splitk_elem_kernel writes), then writes round(g * x / rms(x)) as the next
-// product's A row.  Every load (X, partials, gain) comes before any store.
+// split-K partials in split order into the residual row X, then writes
+// round(g * x / rms(x)) as the next product's A row.  Every load (X, partials,
+// gain) comes before any store.
 constexpr int RN_THREADS = 1024, RN_MAXI = 2;  // rows up to RN_THREADS * 4 * RN_MAXI wide
 __global__ __launch_bounds__(RN_THREADS) void splitk_resid_norm_kernel(GemmParams p, const bf16_t* gain,
                                                                        bf16_t* a_out, float eps) {
