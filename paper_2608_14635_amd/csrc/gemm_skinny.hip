@@ -92,9 +92,9 @@ __global__ __launch_bounds__(256) void splitk_epi_kernel(GemmParams p, int tiles
 // added in wave order, and the epilogue follows in the same kernel: no partial
 // sums in memory, no second launch.
 //
-// HBM-bound on the weights.  A CU can have about 32 KB of loads outstanding
-// (47 GB/s from HBM), shared by the weights and by A's rows from L2, so CB is
-// the smallest that the epilogue allows where that gives every CU a workgroup.
+// HBM-bound on the weights.  A CU has about 32 KB of loads outstanding, shared by
+// the weights and by A's rows from L2 (gemm_tile.hip), so CB is the smallest that
+// the epilogue allows where that gives every CU a workgroup.
 // The eight K ranges also spread the accesses: all workgroups walking K in step
 // through rows 8 KB apart (hidden size 4096) reach 4.6-4.9 TB/s where other
 // row lengths reach 6.

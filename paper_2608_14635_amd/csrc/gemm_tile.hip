@@ -4,11 +4,14 @@
 // and the choice of the tile for every bf16 product.
 //
 // What bounds these products is each CU's operand stream, not its matrix core:
-// about 32 KB of loads can be outstanding per CU, and with weights coming from
-// HBM (0.7 us) that is about 47 GB/s a CU whatever the tile or the depth of the
-// ring (twice the stages gave nothing).  A K tile of (BM + BN) x 64 therefore
-// takes about (BM + BN) * 128 B / 47 GB/s, and a product takes that times its K
-// tiles times the rounds of workgroups over the CUs (tile_cost below).
+// however much a workgroup has issued, about 32 KB of loads are outstanding per
+// CU, and while weights come from HBM with 0.7 us latency that is at most 47 GB/s
+// a CU, A's rows from L2 included, whatever the tile or the depth of the ring
+// (twice the stages gave nothing).  (HBM itself gives 256 CUs 25 GB/s each: the
+// rest of a CU's stream is A and the weights that its neighbours already fetched.)
+// A K tile of (BM + BN) x 64 therefore takes about (BM + BN) * 128 B / 47 GB/s,
+// and a product takes that times its K tiles times the rounds of workgroups over
+// the CUs (tile_cost below).
 //
 // One workgroup of WM x WN waves; K tiles stream with buffer_load_dwordx4 ...
 // lds into a ring of STAGES; fragments are read one K tile ahead of their

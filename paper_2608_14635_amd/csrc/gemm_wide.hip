@@ -16,7 +16,8 @@
 // Operands stream with buffer_load_dwordx4 ... lds into a ring of eight 16 KB
 // half tiles (128 rows x 64 k).  Half tile n of the stream is read in phase n
 // and its slot refilled in phase n+1, when every wave has read it, with half
-// tile n+8: six half tiles (96 KB) stay in flight per CU.  Even K tiles are
+// tile n+8: six half tiles (96 KB) are issued ahead per CU, of which the memory
+// system has about 32 KB outstanding at a time (gemm_tile.hip).  Even K tiles are
 // taken B0 A0 B1 A1, odd ones B1 A0 B0 A1, so each phase needs one new half
 // tile (8 or 4 LDS reads per wave) and the other operand is already in
 // registers.  A ring of ten half tiles was 2 % slower.
@@ -24,8 +25,9 @@
 // Measured on 131072 rows (against a 4-wave kernel of the same tile with
 // 32x32x16 MFMAs, LDS reads interleaved one by one with them and an epilogue
 // through LDS): 4096 columns, K 14336: 11.40 -> 10.19 ms; K 4096: 3.60 -> 3.38.
-// What bounds it is power: 76 % matrix-core busy at 1.81 GHz; with every load
-// served by L2 the same loop takes 9.7 ms.
+// What bounds it is power: the matrix cores are busy 76-86 % of the time at
+// 1.7-1.8 GHz (8B and 32B rebuilds); with every load served by L2 the K 14336
+// product takes 9.7 ms.
 //
 // Workgroups are remapped so that each XCD (dispatch round-robins workgroups
 // over the 8 XCDs) works on a contiguous range of tiles, walked in groups of

@@ -12,13 +12,14 @@ enum Epi : int {
   EPI_RESID = 1,   // X += acc (fp32 residual stream)
   EPI_SWIGLU = 2,  // Hf = silu(gate) * up
   EPI_STORE = 3,   // X = acc (fp32 output, e.g. transposed logits)
-  EPI_PARTIAL = 4, // split-K pass: fp32 partial tile of one K range (see launch_gemm_bf16_splitk)
+  EPI_PARTIAL = 4, // fp32 sums of one K range (launch_gemm_bf16_splitk, launch_gemm_bf16_resid_norm)
 };
 
 enum BMap : int {
   BMAP_PLAIN = 0,   // B rows n of one matrix
   BMAP_QKV = 1,     // rows [0,s0) of Wq, [s0,s1) of Wk, [s1,..) of Wv
-  BMAP_GATEUP = 2,  // tile of BN rows = BN/2 rows of W_gate then the same BN/2 rows of W_up
+  BMAP_GATEUP = 2,  // 2 ffn columns, gate and up: 16 rows of W_gate and the same 16 of W_up in turn
+                    // (EPI_PARTIAL: 128 and 128)
 };
 
 struct EpiParams {

@@ -36,9 +36,8 @@ SHAPES = {
     "qwen25_1_5b_2l": dataclasses.replace(W.QWEN25_1_5B.with_layers(2), vocab=2048),
     # 16 q heads per kv head
     "g16_bf16": dataclasses.replace(W.TINY_BF16, num_q_heads=32, num_kv_heads=2),
-    # a vocabulary of whole 64-row blocks: the LM head runs as a few-row
-    # product into row-major logits (the other bf16 vocabularies here take the
-    # transposed product)
+    # a vocabulary of whole 64-column blocks: row-major logits (tiny_bf16's 1000
+    # columns, no multiple of 16, take the transposed product)
     "tiny_bf16_v1024": dataclasses.replace(W.TINY_BF16, vocab=1024),
     # two layers of the small decoder, for long contexts the oracle still
     # rebuilds in seconds
@@ -53,13 +52,12 @@ CASES["tiny_bf16_40req"] = ("tiny_bf16", [1 + (7 * i) % 90 for i in range(40)], 
 CASES["tiny_bf16_v1024_20req"] = ("tiny_bf16_v1024", [1 + (5 * i) % 60 for i in range(20)], 16)
 CASES["tiny_bf16_v1024_40req"] = ("tiny_bf16_v1024", [1 + (7 * i) % 90 for i in range(40)], 16)
 # the edges of the few-row products: one full 16-row tile, their largest batch
-# (64 rows), and one request more (the general split-K path, with the residual
-# sum and the norm as separate kernels)
+# (64 rows), and one request more (the tiled products)
 CASES["tiny_bf16_v1024_16req"] = ("tiny_bf16_v1024", [1 + (11 * i) % 70 for i in range(16)], 16)
 CASES["tiny_bf16_v1024_64req"] = ("tiny_bf16_v1024", [1 + (13 * i) % 50 for i in range(64)], 16)
 CASES["tiny_bf16_v1024_65req"] = ("tiny_bf16_v1024", [1 + (13 * i) % 50 for i in range(65)], 16)
-# long contexts: 8192 keys split into 128 ranges of 64 keys (the split's cap),
-# a ragged 5000-key context, and 16 requests of 1-2K keys (31 ranges each)
+# long contexts: 8192 keys split into 128 ranges of 64 keys (the most there are),
+# a ragged 5000-key context, and 16 requests of 1-2K keys in ranges of 64
 CASES["tiny_bf16_2l_long"] = ("tiny_bf16_2l", [8192, 5000, 1], 16)
 CASES["tiny_bf16_2l_16req_1k_2k"] = ("tiny_bf16_2l", [1024 + 61 * i for i in range(16)], 16)
 

@@ -1,7 +1,6 @@
 """The bf16 products pick their tile by the row and column counts: a request
 rebuilt alone (small tiles), in a batch of short requests and in a long batch
-(256 x 256 tiles) holds the same bits, for plain, q/k-normed and biased heads;
-decode batches on both sides of the few-row kernel's 64 rows match the oracle."""
+(256 x 256 tiles) holds the same bits, for plain, q/k-normed and biased heads."""
 import dataclasses
 import sys
 
