@@ -20,7 +20,6 @@
 // and register-direct loads (decode_attn_mfma_kernel); the general one
 // serves fp32 models and other head sizes.
 #include <algorithm>
-#include <vector>
 
 #include "common.h"
 #include "launch.h"
@@ -621,18 +620,21 @@ int decode_attn_chunk(int dtype, int block_size, const int32_t* positions, int n
   const int64_t most = decode_attn_max_splits(nkv, max_ctx);
   int64_t chunk = std::max<int64_t>({total * per / target, (max_ctx + most - 1) / most, pairs >= 2048 ? 512 : 64});
   chunk = (chunk + 15) / 16 * 16;
-  // the first length, in steps of a 64th, that makes few enough ranges
-  std::vector<int64_t> steps{chunk};
-  while (steps.back() < max_ctx) steps.push_back(steps.back() + std::max<int64_t>(16, steps.back() / 64 / 16 * 16));
-  auto fits = [&](int64_t c) {
-    int64_t items = 0;
-    for (int r = 0; r < num_requests; ++r) items += (uint32_t)positions[r] / (uint32_t)c + 1;
-    return items * per <= target;
-  };
-  size_t lo = 0, hi = steps.size() - 1;
+  // the first length, in steps of about a 64th (some 1,200 of them up to 2^31), that
+  // makes few enough ranges
+  int64_t steps[2048];
+  int n = 0;
+  for (steps[n++] = chunk; steps[n - 1] < max_ctx && n < 2048; ++n)
+    steps[n] = steps[n - 1] + std::max<int64_t>(16, steps[n - 1] / 64 / 16 * 16);
+  int lo = 0, hi = n - 1;
   while (lo < hi) {
-    const size_t mid = (lo + hi) / 2;
-    if (fits(steps[mid])) hi = mid; else lo = mid + 1;
+    const int mid = (lo + hi) / 2;
+    int64_t items = 0;
+    for (int r = 0; r < num_requests; ++r) items += (uint32_t)positions[r] / (uint32_t)steps[mid] + 1;
+    if (items * per <= target)
+      hi = mid;
+    else
+      lo = mid + 1;
   }
   return (int)steps[lo];
 }
