@@ -598,29 +598,32 @@ int decode_attn_max_splits(int nkv, int64_t max_ctx) {
 // and kv head or more, ranges near whole requests balance badly (8 kv heads, 16
 // requests of 8000: 768 / 1024 / 2048 workgroups 163 / 207 / 174; 128 of 1000:
 // 1536 / 2048 214 / 205).  fp32 has room for one, and 512 in two rounds beat 256
-// on ragged batches (16 of 8000: 482 against 563); from 384 pairs on, 64 of 2000:
-// 768 / 2048 649 / 544.
+// on ragged batches (16 of 8000: 482 against 563); from 384 pairs on, 64 ragged of
+// 2000: 768 / 2048 649 / 544, 64 of 2000 each 441 / 465.
 // Beyond a target's pairs, half as many workgroups again as pairs; where there
 // are 2048 pairs, no range below 512 keys (2048 requests of 100, 8 kv heads in
-// fp32: 1251 with ranges of about 128, 1144 whole).  At least 64 keys, and no
-// more ranges than the partials hold.
+// fp32: 1251 with ranges of about 128, 1144 whole), and in the general kernel none
+// below 256 from 384 pairs on.  At least 64 keys, and no more ranges than the
+// partials hold.
 int decode_attn_chunk(int dtype, int block_size, const int32_t* positions, int num_requests, int nq, int nkv, int d,
                       int64_t max_ctx) {
   const int g = nq / nkv;
   const bool mfma = on_mfma(dtype, block_size, g, d);
   const int64_t per = mfma ? (nkv + 3) / 4 : nkv;  // workgroups per range
   const int64_t pairs = num_requests * per;
+  int64_t total = 0;
+  for (int r = 0; r < num_requests; ++r) total += positions[r] + 1;
+  const bool ragged = max_ctx * num_requests > total + total / 4;
   int64_t target = 512;
   if (mfma && g > 8 && pairs <= 64) target = 256;
   if (!mfma && dtype == 1) target = pairs <= 256 ? 768 : 2048;
-  if (!mfma && dtype == 0 && pairs >= 384) target = 2048;
+  if (!mfma && dtype == 0 && pairs >= 384 && ragged) target = 2048;
   target = std::max<int64_t>(target, (pairs + pairs / 2 + 255) / 256 * 256);
-  int64_t total = 0;
-  for (int r = 0; r < num_requests; ++r) total += positions[r] + 1;
   const int64_t most = decode_attn_max_splits(nkv, max_ctx);
-  int64_t chunk = std::max<int64_t>({total * per / target, (max_ctx + most - 1) / most, pairs >= 2048 ? 512 : 64});
+  const int64_t shortest = pairs >= 2048 ? 512 : !mfma && pairs >= 384 ? 256 : 64;
+  int64_t chunk = std::max<int64_t>({total * per / target, (max_ctx + most - 1) / most, shortest});
   chunk = (chunk + 15) / 16 * 16;
-  // the first length, in steps of about a 64th (some 1,200 of them up to 2^31), that
+  // the first length, in steps of about a 64th (some 1,040 of them up to 2^31), that
   // makes few enough ranges
   int64_t steps[2048];
   int n = 0;
