@@ -90,6 +90,17 @@ __device__ __forceinline__ void acc_resid(const f32x4 (&acc)[RI][CJ], int M, con
   }
 }
 
+// STORE: out = acc (fp32), out on any 4-byte boundary (a caller's logits).
+template <int RI, int CJ, typename Row, typename Col>
+__device__ __forceinline__ void acc_store(const f32x4 (&acc)[RI][CJ], int M, float* out, int64_t ld, Row row,
+                                          Col col) {
+#pragma unroll
+  for (int i = 0; i < RI; ++i)
+    if (row(i) < M)
+#pragma unroll
+      for (int j = 0; j < CJ; ++j) *reinterpret_cast<f32x4_a4*>(out + row(i) * ld + col(j)) = acc[i][j];
+}
+
 // SWIGLU: hf = silu(gate) * up; col(j) counts gate/up columns in pair order,
 // output column = 16 * (col / 32) + col % 16.
 template <int RI, int CJ, typename Row, typename Col>

@@ -218,12 +218,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(GemmParams p, i
     float* out = EPI == EPI_STORE ? p.epi.x : p.part + split * p.part_stride;
     const int64_t ld = EPI == EPI_STORE ? p.epi.ldx : p.part_ld;
     const int nb = EPI == EPI_STORE ? n0 : tile_n * BN;
-#pragma unroll
-    for (int i = 0; i < RI; ++i)
-      if (row(i) < p.M)
-#pragma unroll
-        for (int j = 0; j < CJ; ++j)  // (a caller's logits may start on any float)
-          *reinterpret_cast<f32x4_a4*>(out + row(i) * ld + nb + col(j)) = acc[i][j];
+    acc_store<RI, CJ>(acc, p.M, out + nb, ld, row, col);
   }
 }
 
@@ -259,6 +254,9 @@ int64_t tile_cost(int t, int64_t workgroups) { return (workgroups + CUS - 1) / C
 // The tile of least cost, the larger one on a tie (fewer bytes moved).
 // head_tiles: columns in whole heads (the per-head norm sums one).  64 x 128
 // loses to 128 x 64 wherever both may be used.
+// A plain store of at most 128 rows keeps to 128-row tiles, whatever near ties say
+// (LM head of 128256 columns, K 4096, whole steps: 65 rows 398 us with 128 x 128
+// tiles, 412 with 256 x 256 ones; from 129 rows on 519 and 485).
 int pick_tile(int M, int N, bool head_tiles, bool wide_ok) {
   int best = T128x128;
   int64_t cost = tile_cost(best, tiles_of(best, M, N));
@@ -328,7 +326,7 @@ GemmParams columns(int epi, const GemmParams& p, int c0, int c1) {
 void launch_gemm_bf16(int epi, const GemmParams& p, hipStream_t s) {
   const int N = columns_of(p);
   if (p.M <= 0 || N <= 0) return;
-  const bool heads = epi == EPI_QKV && p.epi.q_norm != nullptr, wide_ok = epi != EPI_STORE;
+  const bool heads = epi == EPI_QKV && p.epi.q_norm != nullptr, wide_ok = epi != EPI_STORE || p.M > 128;
   const int t = pick_tile(p.M, N, heads, wide_ok);
   // A last round of workgroups that is mostly empty costs as much as a full
   // one: where it pays for another launch, whole rounds of one tile take the
@@ -341,7 +339,7 @@ void launch_gemm_bf16(int epi, const GemmParams& p, hipStream_t s) {
   const int64_t tiles = tiles_of(t, p.M, N);
   int64_t cost = tile_cost(t, tiles) * KT * 15 / 16;  // what the costs are good for
   int best1 = -1, cut = 0;
-  if (wide_ok && tiles > CUS && tiles <= 4 * CUS)
+  if (epi != EPI_STORE && tiles > CUS && tiles <= 4 * CUS)
     for (int t1 = T128x128; t1 < TILES; ++t1) {
       const int tiles_m = cdiv(p.M, TILE[t1].bm);
       for (int r = 1; r <= 3; ++r) {

@@ -214,6 +214,8 @@ __global__ __launch_bounds__(NT, 2) void gemm_wide_kernel(GemmParams p, int tile
     acc_qkv<NORM, 8, 4, BM, BN, WAVES, 64>(acc, m0, p.M, n0, p.epi, smem, wave, lane, row, col);
   } else if constexpr (EPI == EPI_RESID) {
     acc_resid<8, 4, 4>(acc, p.M, p.epi, row, ocol);
+  } else if constexpr (EPI == EPI_STORE) {
+    acc_store<8, 4>(acc, p.M, p.epi.x, p.epi.ldx, row, ocol);
   } else {
     acc_swiglu<8, 4>(acc, p.M, p.epi, row, ocol);
   }
@@ -236,6 +238,8 @@ void launch_gemm_wide(int epi, const GemmParams& p_in, hipStream_t s) {
     hipLaunchKernelGGL(gemm_wide_kernel<EPI_QKV>, grid, block, 0, s, p, tiles_m, tiles_n);
   else if (epi == EPI_RESID)
     hipLaunchKernelGGL(gemm_wide_kernel<EPI_RESID>, grid, block, 0, s, p, tiles_m, tiles_n);
+  else if (epi == EPI_STORE)
+    hipLaunchKernelGGL(gemm_wide_kernel<EPI_STORE>, grid, block, 0, s, p, tiles_m, tiles_n);
   else
     hipLaunchKernelGGL(gemm_wide_kernel<EPI_SWIGLU>, grid, block, 0, s, p, tiles_m, tiles_n);
 }

@@ -82,7 +82,7 @@ int launch_probe(int* dev_flag, hipStream_t s);
 
 // GEMMs with fused epilogues
 void launch_gemm_bf16(int epi, const GemmParams& p, hipStream_t s);  // picks the tile
-void launch_gemm_wide(int epi, const GemmParams& p, hipStream_t s);  // 256 x 256 tiles: QKV, RESID, SWIGLU
+void launch_gemm_wide(int epi, const GemmParams& p, hipStream_t s);  // 256 x 256 tiles
 void launch_gemm_f32(int epi, const GemmParams& p, hipStream_t s);
 // The tiled product as fp32 partial sums of K ranges (EPI_PARTIAL, columns in
 // plain order): tile and K ranges of least cost whose partials fit part_cap

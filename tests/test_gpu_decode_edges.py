@@ -29,6 +29,9 @@ CASES = {
     "20req_norm_bias": (dataclasses.replace(T2, vocab=1024, qk_norm=True, qkv_bias=True),
                         [1 + (7 * i) % 60 for i in range(20)], 0),
     "70req_norm": (dataclasses.replace(T2, vocab=1024, qk_norm=True), [1 + (7 * i) % 60 for i in range(70)], 0),
+    # vocabularies large enough for 256 x 256 tiles: row-major and transposed
+    "300req_vocab_152064": (dataclasses.replace(T2, num_layers=1, hidden=256, vocab=152064), [1 + i % 5 for i in range(300)], 1),
+    "3req_vocab_152065": (dataclasses.replace(T2, num_layers=1, hidden=256, vocab=152065), [2, 40, 17], 1),
     "4req_unaligned_logits": (dataclasses.replace(T2, vocab=1024), [3, 40, 15, 16], 1),
 }
 
